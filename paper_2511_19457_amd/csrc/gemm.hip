@@ -28,6 +28,8 @@
 // are those of the dense variant, and a skipped chunk would only have added
 // exact zeros, the skip output equals the dense output bit for bit (for
 // finite weights).
+#include <type_traits>
+
 #include "commit.h"
 #include "common.h"
 #include "dtype.h"
@@ -64,7 +66,11 @@ struct GemmArgs {
   // per split, chunks per tap, kernel rows, and the reciprocals of the
   // divisors rounded once (float divmod)
   int ntn32, ntmn32, cpt32, kh32;
-  float inv_ntn, inv_ntmn, inv_cpt, inv_kw, inv_dh, inv_dw;
+  float inv_ntmn, inv_cpt, inv_kw, inv_dh, inv_dw;
+  // column groups of the tile walk: gw column tiles a group (the last one
+  // lastw), gt = row tiles x gw
+  int gw32, gt32, lastw32;
+  float inv_gt, inv_gw, inv_lastw;
   int act;
   int split;
   DeviceRoute route;
@@ -97,8 +103,6 @@ __device__ __forceinline__ f32x4 mfma_chunk(const char *a_row, const char *b_row
     return acc;
   }
 }
-
-__device__ __forceinline__ int64_t cdiv_dev(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // q = n / d, r = n % d for 0 <= n < 2^24 and 0 < d < 2^24: the float
 // quotient is within one of the true one, then one integer correction,
@@ -521,237 +525,313 @@ __global__ __launch_bounds__(256) void split_reduce_group(ReduceGroup g) {
 // C_in % 64 == 0.  A K chunk is 64 channels of one tap, so the tap and
 // channel offset of a chunk are work-group-uniform scalars (no per-vector
 // division), and a thread's gathered pixels only move by the tap offset.
-// Work-group = WGM x WGN waves; a wave owns WTM x WTN MFMA 16x16 blocks,
-// which sets the LDS bytes read per MFMA.  Chunks are staged global ->
-// registers -> LDS (swizzled 128-byte rows: conflict-free 16-byte reads and
-// writes), double-buffered, one barrier per
-// 64-wide chunk (two MFMA k-steps).  Gathers are branch-free (out-of-image
-// taps read a valid address and are zeroed) so all of a thread's loads are
-// in flight together.  Tiles are ordered so that each XCD works on a
-// contiguous range of output rows (neighbouring tiles share input halos in
-// that XCD's L2).  The skip form walks only the (tap, 64-channel) chunks in
-// which some gathered pixel of the tile is nonzero, in dense order, so its
-// output equals the dense form's bit for bit.
+// Work-group = WGM x WGN waves; a wave owns 16 WTM pixels x 16 WTN channels,
+// which sets the LDS bytes read per MFMA.  Chunks go straight from memory to
+// a ring of S stages in LDS (buffer loads with an LDS destination: no staging
+// registers and no LDS write instructions); a tap outside the image has its
+// offset past the descriptor's range and lands as zeros.  One barrier per
+// chunk; a wave reads a chunk's MFMA operands from LDS, and sends the loads
+// that refill the stage freed by the barrier, between the MFMAs of the chunk
+// before.  The MFMA's rows are channels, so a lane ends with 16 consecutive
+// output channels of a pixel and the epilogue needs no LDS.
+// Bounds, measured with the other parts switched off (4096^3 fp16, 128 x 256:
+// 117 us): MFMAs alone 97 us (1.6 PFLOP/s with its start and end), loads
+// alone 95 us (17 TB/s out of the L2s); small tiles are bound by the loads
+// (64 x 64: 293 us with or without MFMAs).  Against the form that staged
+// chunks through registers, with two barriers' worth of LDS writes and an
+// epilogue through LDS: 4096^3 155 -> 117 us; 2048 x 768 x 3072 31 -> 19 us;
+// 3 x 3 512 -> 512 at 7 x 7, N = 32 29 -> 18 us; 3 x 3 256 -> 256 at 56 x 56,
+// N = 32 164 -> 137 us; K = 64 alone (start and epilogue), 4096 x 4096 20 ->
+// 12 us.  The ring's depth, beyond what one chunk's MFMAs cover, and more
+// waves of smaller tiles change nothing; branches and scalar arithmetic in
+// the loop did (a step written with guards: 20 % slower).
+// Work-groups walk their tiles XCD by XCD (tile_of).  The skip form walks
+// only the (tap, 64-channel) chunks in which some gathered pixel of the tile
+// is nonzero, in dense order, so its output equals the dense form's bit for
+// bit.
 constexpr int kBK2 = 64;
 constexpr int kMaxChunks2 = 1024;          // K <= 65536 on the skip path
+
+// s_waitcnt immediate: at most n vector-memory operations outstanding, the
+// other counters not waited for.
+constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
+constexpr int kLgkmcnt0 = 15 | (7 << 4) | (3 << 14);   // LDS operations done
+
+// Waits until all but the `chunks` <= C newest chunks' loads (L per chunk) of
+// this wave have landed.
+template <int C, int L>
+__device__ __forceinline__ void wait_chunks(int chunks) {
+  static_assert(C * L < 64, "vmcnt range");
+  if constexpr (C > 0) {
+    if (chunks < C) return wait_chunks<C - 1, L>(chunks);
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(C * L));
+}
+
+// A 16-byte-per-lane buffer load whose data goes to LDS: lane l's 16 bytes
+// land at LDS address lds + 16 l (lds uniform), zeros where the offset lies
+// past the descriptor's range.  In assembly and not by the builtin: the
+// compiler cannot tell the ring's stages apart and would wait for every load
+// in flight before each LDS read; the waits are written out at the barriers
+// instead (wait_loads).  No register is written, so the compiler's own
+// counting of other loads only waits longer than it has to.  (One wait state
+// between the write of m0 and its use.)
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t lds, int voffset, int soffset) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds), "v"(voffset), "s"(rsrc), "s"(soffset)
+               : "memory");
+}
+__device__ __forceinline__ u32x4 buffer_words(const void *p, int64_t bytes) {
+  const uint64_t b = reinterpret_cast<uint64_t>(p);
+  return u32x4{(uint32_t)b, (uint32_t)(b >> 32) & 0xFFFFu, (uint32_t)bytes, (uint32_t)kBufDword3};
+}
+
+// Tile walk of the second-generation kernels: work-group -> (K split, row
+// tile, column tile).  Work-groups are dealt round-robin to the 8 XCDs, so
+// XCD i gets the i-th contiguous range of tile ids, and a tile id walks
+// (split, column group, row tile, column tile of the group) with the column
+// tiles innermost: the tiles that gather the same input rows run together in
+// one XCD's L2.  The groups (host: ig_column_groups) keep an XCD to a part
+// of the weights where these are what its L2 would re-read.  (32-bit
+// arithmetic with float-reciprocal division: a 64-bit division by a runtime
+// value is a long scalar sequence on the critical path of every
+// work-group's start.)
+struct TileId {
+  int tile, zsplit, mt, nt;
+};
+__device__ __forceinline__ TileId tile_of(const GemmArgs &a) {
+  TileId t;
+  const int vid = (int)blockIdx.x, ntiles = (int)gridDim.x;
+  // (XCD i holds the i-th range: q + 1 tiles for the first r XCDs, q after)
+  t.tile = (vid & 7) * (ntiles >> 3) + min(vid & 7, ntiles & 7) + (vid >> 3);
+  int rest, grp;
+  divmod_small(t.tile, a.ntmn32, a.inv_ntmn, t.zsplit, rest);
+  divmod_small(rest, a.gt32, a.inv_gt, grp, rest);
+  const bool last = (grp + 1) * a.gw32 >= a.ntn32;
+  divmod_small(rest, last ? a.lastw32 : a.gw32, last ? a.inv_lastw : a.inv_gw, t.mt, t.nt);
+  t.nt += grp * a.gw32;
+  return t;
+}
+
+// Chunk j of the walk (C channels of ESZ bytes of one tap) as its loads need
+// it: 31 - r | 31 - s << 5 | kofs / 16 << 10, with the kernel row r and column
+// s of its tap and its byte offset kofs < 2^18 in a weight row.
+template <int C, int ESZ>
+__device__ __forceinline__ uint32_t walk_entry(const GemmArgs &a, int j) {
+  int t, cb, r, sx;
+  divmod_small(j, a.cpt32, a.inv_cpt, t, cb);
+  divmod_small(t, (int)a.Kw, a.inv_kw, r, sx);
+  return (uint32_t)((31 - r) | (31 - sx) << 5 | ((t * (int)a.Cin + cb * C) * ESZ / 16) << 10);
+}
+// A walk entry read as scalars (it is the same in every lane).  xofs: byte
+// offset of the chunk's channels from a row's first gathered pixel, from kofs
+// and the per-row and per-column differences of the two layouts.
+struct WalkStep {
+  int kofs, xofs;
+  uint32_t rsh, ssh;   // 31 - r, 31 - s: moves tap bit r / s to bit 31
+};
+struct WalkGeom {
+  uint32_t dr, ds, base;
+};
+template <int ESZ>
+__device__ __forceinline__ WalkGeom walk_geom(const GemmArgs &a) {
+  WalkGeom g;
+  g.dr = (uint32_t)(((int)a.dh * (int)a.W - (int)a.Kw) * (int)a.Cin * ESZ);
+  g.ds = (uint32_t)(((int)a.dw - 1) * (int)a.Cin * ESZ);
+  g.base = 31u * (g.dr + g.ds);
+  return g;
+}
+__device__ __forceinline__ WalkStep walk_step(const WalkGeom &g, uint32_t entry) {
+  const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)entry);
+  WalkStep w;
+  w.rsh = e & 31u;
+  w.ssh = e >> 5 & 31u;
+  w.kofs = (int)(e >> 10 << 4);
+  w.xofs = (int)((uint32_t)w.kofs + g.base - w.rsh * g.dr - w.ssh * g.ds);
+  return w;
+}
+
+// ORs the bitmap bits of every pixel that rows [m0, m0 + rows) gather at
+// every tap into nzvec, bit tap * (C_in / 8) + channel block (plus a cleared
+// spare word for windows past the end).  Whole work-group, NT threads; ends
+// with a barrier.  (32-bit index arithmetic: pixel indices are below 2^24.)
+template <int NT>
+__device__ __forceinline__ void gather_nonzero_bits(const GemmArgs &a, int m0, int rows,
+                                                    uint32_t *nzvec) {
+  const int tid = threadIdx.x;
+  const int H = (int)a.H, W = (int)a.W, Ho = (int)a.Ho, Wo = (int)a.Wo, kw = (int)a.Kw;
+  const int cpg = (int)(a.Cin / 8);  // bitmap blocks per pixel
+  const int kv_words = (int)((a.taps * cpg + 31) / 32) + 1;
+  for (int i = tid; i < kv_words; i += NT) nzvec[i] = 0u;
+  __syncthreads();
+  const int taps = (int)a.taps, ntp = rows * taps;
+  const float inv_taps = 1.0f / (float)taps, inv_kw = 1.0f / (float)kw;
+  for (int p = tid; p < ntp; p += NT) {
+    int r_in, tap, t1, ow, nn, oh, r, sx;
+    divmod_small(p, taps, inv_taps, r_in, tap);
+    const int m = m0 + r_in;
+    if (m >= (int)a.M) continue;
+    divmod_small(m, Wo, a.inv_wo, t1, ow);
+    divmod_small(t1, Ho, a.inv_ho, nn, oh);
+    divmod_small(tap, kw, inv_kw, r, sx);
+    const int ih = oh * (int)a.sh - (int)a.ph + r * (int)a.dh;
+    const int iw = ow * (int)a.sw - (int)a.pw + sx * (int)a.dw;
+    if (ih < 0 || ih >= H || iw < 0 || iw >= W) continue;
+    const int64_t pix = ((int64_t)nn * H + ih) * W + iw;
+    for (int b = 0; b < cpg; b += 32) {
+      const int nb = min(32, cpg - b);
+      lds_or_bits(nzvec, tap * cpg + b, read_bits(a.mask, pix * cpg + b, nb), nb);
+    }
+  }
+  __syncthreads();
+}
+
+// Whether chunk j (channels [C cb, min(C cb + C, Cin)) of tap t) has a
+// nonzero: up to C / 8 bits from bit t cpg + (C / 8) cb of nzvec -- PART:
+// read through a 64-bit window, since with cpg % (C / 8) != 0 they may
+// straddle a word; whole chunks: inside one word.
+template <int C, bool PART>
+__device__ __forceinline__ bool chunk_nonzero(const GemmArgs &a, const uint32_t *nzvec, int j) {
+  const int cpg = (int)(a.Cin / 8);
+  int t, cb;
+  divmod_small(j, a.cpt32, a.inv_cpt, t, cb);
+  const int pos = t * cpg + (C / 8) * cb;
+  if constexpr (PART) {
+    const int nb = min(C / 8, cpg - (C / 8) * cb);
+    const uint64_t win = (uint64_t)nzvec[pos >> 5] | ((uint64_t)nzvec[(pos >> 5) + 1] << 32);
+    return ((win >> (pos & 31)) & ((1ull << nb) - 1ull)) != 0ull;
+  } else {
+    return ((nzvec[pos >> 5] >> (pos & 31)) & ((1u << (C / 8)) - 1u)) != 0u;
+  }
+}
+
+// Split execution: a row tile's own route, from the zero counts of the
+// samples its rows come from (one double division, >=, as sparoa_route).
+__device__ __forceinline__ bool split_route_skips(const GemmArgs &a, int m0, int rows) {
+  const int64_t last = min((int64_t)m0 + rows, a.M) - 1;
+  const int64_t s0 = m0 / a.route.rows_per_sample, s1 = last / a.route.rows_per_sample;
+  unsigned long long z = 0;
+  for (int64_t q = s0; q <= s1; ++q) z += a.route.sample_zeros[q];
+  const double n = (double)((unsigned long long)(s1 - s0 + 1) *
+                            (unsigned long long)a.route.sample_numel);
+  return (double)z / n >= a.route.sparsity_thr;
+}
 
 // PART: C_in % 64 != 0, a tap's last chunk is partial (a separate
 // instantiation: the per-lane channel test and the per-chunk weight offset
 // cost the whole-chunk kernels up to 10 %).
-template <int DT, int WGM, int WGN, int WTM, int WTN, int PF, int KS, bool SKIP, bool PART>
+template <int DT, int WGM, int WGN, int WTM, int WTN, int S, bool PART>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
-  constexpr int NT = 64 * WGM * WGN;   // threads per work-group
-  constexpr int BKC = 32 * KS;         // channels per chunk (KS MFMA k-steps)
-  // LDS rows of 128 bytes with 16-byte vector v of row r stored at slot
-  // v ^ (r & 7): the vectors of one column in any 8 consecutive rows sit in
-  // distinct banks, so the 16-byte writes and MFMA-operand reads are free of
-  // bank conflicts without padding (measured as fast as 160-byte padded rows
-  // and 20 % smaller).
-  constexpr int ROW = BKC * 2;
-  constexpr int VPR = BKC / 8;         // 16-byte vectors per chunk row
+  constexpr int NW = WGM * WGN;        // waves
+  constexpr int NT = 64 * NW;          // threads per work-group
+  constexpr int ROW = kBK2 * 2;        // bytes of a chunk row: 8 vectors of 16 bytes
   using E = Elem<DT>;
+  using raw = typename E::raw;
   static_assert(E::size == 2, "16-bit types");
-  static_assert(VPR == 8, "swizzle of 8-vector rows");
   constexpr int BM = WGM * 16 * WTM, BN = WGN * 16 * WTN;
-  constexpr int AV = BM * VPR / NT;  // 16-byte A vectors per thread per chunk
-  constexpr int BV = BN * VPR / NT;
-  constexpr int RPU = NT / VPR;       // rows covered by one vector slot u
-  static_assert(AV >= 1 && BV >= 1, "tile too small");
-  static_assert(RPU % 8 == 0, "a thread's rows agree mod 8");
-  constexpr int CS = BN + 4;  // fp32 row stride of the epilogue's staged tile
-  constexpr int STAGE = 2 * (BM + BN) * ROW;
-  constexpr int SMEM = STAGE > BM * CS * 4 ? STAGE : BM * CS * 4;
+  // a wave's 16-byte LDS-destination load covers 8 chunk rows
+  constexpr int AV = BM / 8 / NW, BV = BN / 8 / NW;
+  static_assert(AV >= 1 && BV >= 1 && BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile too small");
+  static_assert(WTN % 4 == 0 && NW % 4 == 0, "a lane's 16 channels; B row swizzle");
+  constexpr int L = AV + BV;           // loads in flight per wave and chunk
+  constexpr int NG = WTN / 4;          // 64-channel groups of a wave
+  constexpr int STAGE = (BM + BN) * ROW;
 
-  __shared__ __attribute__((aligned(16))) char smem_raw[SMEM];
-  auto stage = [&](int buf) __attribute__((always_inline)) -> char * {
-    return smem_raw + buf * ((BM + BN) * ROW);
-  };
-  // the chunks this tile walks, in order, each packed as
-  // j | cb << 10 | r << 20 | s << 25 (chunk id, channel block within the
-  // tap, kernel row and column): the walk needs no division per chunk
-  __shared__ int list[kMaxChunks2];
-  __shared__ uint32_t nzvec[SKIP ? kMaxVecWords + 1 : 1];
+  __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
+  __shared__ uint32_t list[kMaxChunks2];   // the chunks this tile walks, in order (walk_entry)
+  __shared__ uint32_t nzvec[kMaxVecWords + 1];
   __shared__ int list_len;
-  __shared__ uint8_t ombytes[BM * (BN / 64 > 0 ? BN / 64 : 1)];   // output bitmap bytes of the tile
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  // XCD-aware order on a 1-D grid: work-groups are dealt round-robin to the 8
-  // XCDs, so XCD i gets the i-th contiguous range of tile ids, and a tile id
-  // walks (split, row tile, column tile) with the column tiles innermost: the
-  // tiles that gather the same input rows run together in one XCD's L2.
-  // (tile arithmetic in 32 bits with float-reciprocal division: a 64-bit
-  // division by a runtime value is a long scalar sequence on the critical
-  // path of every work-group's start)
   // The set-up's kernel arguments are requested in one round trip: this
   // empty statement needs them at the top (the compiler otherwise loads each
   // group just before its first use, behind branches, one round trip each).
   asm volatile("" ::"s"(a.M), "s"(a.N), "s"(a.H), "s"(a.W), "s"(a.Cin), "s"(a.Ho), "s"(a.Wo),
                "s"(a.Kw), "s"(a.sh), "s"(a.sw), "s"(a.ph), "s"(a.pw), "s"(gridDim.x),
                "s"(a.route.counts), "s"(a.route.path_out), "s"(a.om_counts));
-  const int ntiles = (int)gridDim.x;   // row tiles x column tiles x splits
-  const bool om = BN % 64 == 0 && a.om_counts != nullptr;
-  // the device route's counts, requested first as vector loads (in-order
-  // counters: waiting for them later does not wait for the loads behind
-  // them; a scalar load would make the first kernel-argument use wait for
-  // it): their latency overlaps the tile's offset arithmetic and the dense
-  // walk's list writes
-  u32x4 rcq[2] = {u32x4{0u, 0u, 0u, 0u}, u32x4{0u, 0u, 0u, 0u}};
-  if (SKIP && !a.route.sample_zeros && a.route.counts) {
-    const __amdgpu_buffer_rsrc_t cr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)a.route.counts, (short)0, (int)sizeof(sparoa_counts), kBufDword3);
-    rcq[0] = __builtin_amdgcn_raw_buffer_load_b128(cr, 0, 0, 0);
-    rcq[1] = __builtin_amdgcn_raw_buffer_load_b128(cr, 16, 0, 0);
-  }
-  // one tile; returns its output's zero count and nonzero-block count
-  auto tile_body = [&](const int vid) __attribute__((always_inline)) -> uint2 {
-  // (XCD i holds the i-th range: q + 1 tiles for the first r XCDs, q after)
-  const int tile = (vid & 7) * (ntiles >> 3) + min(vid & 7, ntiles & 7) + (vid >> 3);
-  int zsplit_, rest, mt, nt;
-  divmod_small(tile, a.ntmn32, a.inv_ntmn, zsplit_, rest);
-  divmod_small(rest, a.ntn32, a.inv_ntn, mt, nt);
-  const int64_t zsplit = zsplit_;
-  const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * BN;
-  const bool first_tile = tile == 0;
-  const bool first_col = nt == 0;
+  const bool om = a.om_counts != nullptr;
+  // the device route's counts: their latency overlaps the tile's offset
+  // arithmetic and the dense walk's list writes
+  const RouteCountsReq rq = route_counts_request(a.route);
+  const TileId tl = tile_of(a);
+  const int zsplit = tl.zsplit;
+  const int m0 = tl.mt * BM, n0 = tl.nt * BN;
+  const bool first_tile = tl.tile == 0, first_col = tl.nt == 0;
   const int cps = (int)a.chunks_per_split;
-  const int c_begin = zsplit_ * cps;
+  const int c_begin = zsplit * cps;
   const int c_end = min(c_begin + cps, (int)a.nchunks);
-  const int cpt = a.cpt32;   // chunks per tap
-  const float inv_cpt = a.inv_cpt, inv_kw_ = a.inv_kw;
-  auto pack_chunk = [&](int j) __attribute__((always_inline)) -> int {
-    int t, cb, r, sx;
-    divmod_small(j, cpt, inv_cpt, t, cb);
-    divmod_small(t, (int)a.Kw, inv_kw_, r, sx);
-    return j | (cb << 10) | (r << 20) | (sx << 25);
-  };
-  const int cg = tid % VPR;             // this thread's 16-byte column of a chunk row
-  const int rr = tid / VPR;             // this thread's first chunk row
+  const int M = (int)a.M, N = (int)a.N;
 
-  // ---- gathered pixels of this thread's A rows (fixed over the K loop).
+  // ---- LDS layout and this lane's share of the loads.  A wave's load fills
+  // 8 rows of 128 bytes, lane l the slot l & 7 of row l >> 3.  Rows hold
+  // their 16-byte vectors swizzled: slot = vector ^ f(row), so that the
+  // operand reads of any 8 consecutive lanes hit distinct banks.  Pixel rows
+  // are read 16 consecutive ones at a time, f = row & 7.  Channel rows are
+  // read in the order that leaves a lane 16 consecutive output channels
+  // (MFMA row 4 q + t of block b is channel 16 q + 4 b + t of its group of
+  // 64), f = (row >> 4 & 1) * 4 + (row & 3).
+  const int lrow = lane >> 3;
+  const int cgA = (lane & 7) ^ lrow;
+  const int cgB = (lane & 7) ^ ((((wave >> 1) & 1) << 2) | (lrow & 3));
+
+  // ---- gathered pixels of this lane's A rows (fixed over the K loop).
   // Loads go through buffer descriptors: a 32-bit byte offset per lane, and
   // an offset past the end (taps in the padding) reads 0 without touching
-  // memory.  vt[u] has bit t set when tap t of row u lies inside the image.
-  const __amdgpu_buffer_rsrc_t xr =
-      __builtin_amdgcn_make_buffer_rsrc((void *)a.x, (short)0, (int)a.x_bytes, kBufDword3);
-  const __amdgpu_buffer_rsrc_t wr =
-      __builtin_amdgcn_make_buffer_rsrc((void *)a.w, (short)0, (int)a.w_bytes, kBufDword3);
-  int a_offb[AV];      // byte offset of (n, h0, w0, channel cg*8)
-  uint32_t vrow[AV], vcol[AV];  // bit r / s: kernel row r / column s lies inside the image
+  // memory.
+  const u32x4 xr = buffer_words(a.x, a.x_bytes), wr = buffer_words(a.w, a.w_bytes);
+  int a_offb[AV];      // byte offset of (n, h0, w0, channel cgA*8)
+  uint32_t orow[AV], ocol[AV];  // bit r / s: kernel row r / column s lies outside the image
   const int H = (int)a.H, W = (int)a.W, Ho = (int)a.Ho, Wo = (int)a.Wo, Cin = (int)a.Cin;
   const int kw = (int)a.Kw, dh = (int)a.dh, dw = (int)a.dw;
   const float inv_wo = a.inv_wo, inv_ho = a.inv_ho;
 #pragma unroll
   for (int u = 0; u < AV; ++u) {
-    const int m = (int)m0 + rr + RPU * u;
-    const int mm = m < (int)a.M ? m : 0;
+    const int m = m0 + 8 * (u * NW + wave) + lrow;
+    const int mm = m < M ? m : 0;
     int t1, ow, nn, oh;
     divmod_small(mm, Wo, inv_wo, t1, ow);
     divmod_small(t1, Ho, inv_ho, nn, oh);
     const int h0 = oh * (int)a.sh - (int)a.ph, w0 = ow * (int)a.sw - (int)a.pw;
-    a_offb[u] = (((nn * H + h0) * W + w0) * Cin + cg * 8) * 2;
-    vrow[u] = taps_inside(h0, H, a.kh32, dh, a.inv_dh);
-    vcol[u] = taps_inside(w0, W, kw, dw, a.inv_dw);
+    a_offb[u] = (((nn * H + h0) * W + w0) * Cin + cgA * 8) * 2;
+    orow[u] = ~taps_inside(h0, H, a.kh32, dh, a.inv_dh);
+    ocol[u] = ~taps_inside(w0, W, kw, dw, a.inv_dw);
   }
   int b_offb[BV];
 #pragma unroll
   for (int u = 0; u < BV; ++u) {
-    const int jn = (int)n0 + rr + RPU * u;
-    b_offb[u] = ((jn < (int)a.N ? jn : 0) * (int)a.K + cg * 8) * 2;
+    const int jn = n0 + 8 * (u * NW + wave) + lrow;
+    b_offb[u] = ((jn < N ? jn : 0) * (int)a.K + cgB * 8) * 2;
   }
 
-  // ---- skip list ---------------------------------------------------------
+  // ---- the walk: the dense one is written while the route's counts are in
+  // flight; a skipping tile overwrites it with its list.  Skipping: by the
+  // tile's own samples (split execution), by the device route, or because the
+  // host chose the skip path (a bitmap and neither of them).
   int count = c_end - c_begin;
-  bool use_list = SKIP;
-  bool prefilled = false;   // the list already holds the dense walk
-  if constexpr (SKIP) {
-    if (a.route.sample_zeros) {
-      // split execution: this tile's own route, from the zero counts of the
-      // samples its rows come from (one double division, >=, as sparoa_route)
-      const int64_t last = min(m0 + BM, a.M) - 1;
-      const int64_t s0 = m0 / a.route.rows_per_sample, s1 = last / a.route.rows_per_sample;
-      unsigned long long z = 0;
-      for (int64_t q = s0; q <= s1; ++q) z += a.route.sample_zeros[q];
-      const double n = (double)((unsigned long long)(s1 - s0 + 1) *
-                                (unsigned long long)a.route.sample_numel);
-      use_list = (double)z / n >= a.route.sparsity_thr;
-      if (!use_list && a.executed && first_col && tid == 0 && count)
-        atomicAdd(a.executed, (unsigned long long)count);  // a dense tile runs every chunk
-    } else if (a.route.counts) {
-      // the dense walk is written while the route's counts are in flight
-      // (a dense-routed tile then waits for them only once); a skip-routed
-      // tile overwrites it with its list
-      for (int i = tid; i < (int)count; i += NT) list[i] = pack_chunk((int)c_begin + i);
-      prefilled = true;
-      uint32_t rw[8];   // the same in every lane: scalars, so the route is uniform
-#pragma unroll
-      for (int q = 0; q < 8; ++q) rw[q] = __builtin_amdgcn_readfirstlane(rcq[q >> 2][q & 3]);
-      sparoa_counts rc;
-      __builtin_memcpy(&rc, rw, sizeof(rc));
-      use_list = route_skip_counts(rc, a.route.sparsity_thr, a.route.mode);
-      if (a.route.path_out && first_tile && tid == 0)
-        *a.route.path_out = (use_list ? 1u : 0u) | ((uint32_t)a.route.bw_bit << 1);
-    }
-  }
-  if constexpr (!SKIP) {
+  for (int i = tid; i < count; i += NT) list[i] = walk_entry<kBK2, 2>(a, c_begin + i);
+  bool use_list = a.mask != nullptr;
+  if (a.route.sample_zeros) {
+    use_list = split_route_skips(a, m0, BM);
+    if (!use_list && a.executed && first_col && tid == 0 && count)
+      atomicAdd(a.executed, (unsigned long long)count);  // a dense tile runs every chunk
+  } else {
+    if (a.route.counts) use_list = route_counts_skip(rq, a.route);
     if (a.route.path_out && first_tile && tid == 0)
-      *a.route.path_out = (uint32_t)a.route.bw_bit << 1;
+      *a.route.path_out = (a.route.counts && use_list ? 1u : 0u) | ((uint32_t)a.route.bw_bit << 1);
   }
-  if (SKIP && use_list) {
-    const int cpg = (int)(a.Cin / 8);  // bitmap blocks per pixel
-    const int kv_words = (int)((a.taps * cpg + 31) / 32) + 1;   // + the window's spare word
-    for (int i = tid; i < kv_words; i += NT) nzvec[i] = 0u;
-    __syncthreads();
-    // (32-bit index arithmetic with float-reciprocal division: pixel
-    // indices are below 2^24 on this kernel)
-    const int taps = (int)a.taps, ntp = BM * taps;
-    const float inv_taps = 1.0f / (float)taps, inv_kw = 1.0f / (float)kw;
-    for (int p = tid; p < ntp; p += NT) {
-      int r_in, tap, t1, ow, nn, oh, r, sx;
-      divmod_small(p, taps, inv_taps, r_in, tap);
-      const int m = (int)m0 + r_in;
-      if (m >= (int)a.M) continue;
-      divmod_small(m, Wo, inv_wo, t1, ow);
-      divmod_small(t1, Ho, inv_ho, nn, oh);
-      divmod_small(tap, kw, inv_kw, r, sx);
-      const int ih = oh * (int)a.sh - (int)a.ph + r * dh, iw = ow * (int)a.sw - (int)a.pw + sx * dw;
-      if (ih < 0 || ih >= H || iw < 0 || iw >= W) continue;
-      const int64_t pix = ((int64_t)nn * H + ih) * W + iw;
-      for (int b = 0; b < cpg; b += 32) {
-        const int nb = min(32, cpg - b);
-        lds_or_bits(nzvec, tap * cpg + b, read_bits(a.mask, pix * cpg + b, nb), nb);
-      }
-    }
-    __syncthreads();
+  if (use_list) {
+    gather_nonzero_bits<NT>(a, m0, BM, nzvec);
     if (wave == 0) {
       int total = 0;
       for (int base = c_begin; base < c_end; base += 64) {
         const int j = base + lane;
-        bool nz = false;
-        if (j < c_end) {
-          // chunk j = channels [BKC cb, min(BKC cb + BKC, Cin)) of tap t:
-          // up to BKC / 8 bitmap bits from bit t cpg + (BKC / 8) cb, read
-          // through a 64-bit window (with cpg % 8 != 0 they may straddle a
-          // word; the word past the last is cleared)
-          // (whole chunks: BKC / 8 bits at a multiple of BKC / 8, inside
-          // one word)
-          static_assert(BKC / 8 <= 32, "chunk bits in a 64-bit window");
-          int t, cb;
-          divmod_small(j, cpt, inv_cpt, t, cb);
-          const int pos = t * cpg + (BKC / 8) * cb;
-          if constexpr (PART) {
-            const int nb = min(BKC / 8, cpg - (BKC / 8) * cb);
-            const uint64_t win =
-                (uint64_t)nzvec[pos >> 5] | ((uint64_t)nzvec[(pos >> 5) + 1] << 32);
-            nz = ((win >> (pos & 31)) & ((1ull << nb) - 1ull)) != 0ull;
-          } else {
-            constexpr uint32_t kBits = BKC / 8 >= 32 ? 0xFFFFFFFFu : ((1u << (BKC / 8)) - 1u);
-            nz = ((nzvec[pos >> 5] >> (pos & 31)) & kBits) != 0u;
-          }
-        }
+        const bool nz = j < c_end && chunk_nonzero<kBK2, PART>(a, nzvec, min(j, c_end - 1));
         const uint64_t bal = __ballot(nz);
         const int before = __popcll(bal & ((1ull << lane) - 1ull));
-        if (nz) list[total + before] = pack_chunk(j);
+        if (nz) list[total + before] = walk_entry<kBK2, 2>(a, j);
         total += __popcll(bal);
       }
       if (lane == 0) {
@@ -764,45 +844,25 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
     count = list_len;
   }
 
-  // ---- staging: a ring of PF chunks in registers, two chunks in LDS --------
-  u32x4 ra[PF][AV], rb[PF][BV];  // native vectors: no struct copies, stays in VGPRs
-  // valid == false: every offset out of range, the loads return zeros without
-  // touching memory -- the prologue issues its PF + 1 loads unconditionally,
-  // so the compiler can count the loads in flight at the loop head (a
-  // conditional prologue load made it wait for the whole ring there)
-  auto load_chunk = [&](int info, u32x4 (&ra_s)[AV], u32x4 (&rb_s)[BV], bool valid)
-                        __attribute__((always_inline)) {
-    const int j = info & 1023, cb = (info >> 10) & 1023;
-    const int r = (info >> 20) & 31, sx = (info >> 25) & 31;
-    const int tap_offb = ((r * dh * W + sx * dw) * Cin + cb * BKC) * 2;
-    // PART: this lane's 8 channels of the chunk exist (channels past C_in in
-    // the last chunk of a tap read zero on both sides), and the chunk starts
-    // at K index (r kw + sx) C_in + BKC cb of a weight row (whole chunks:
-    // at BKC j)
-    const bool col = PART ? valid && cb * BKC + cg * 8 < Cin : valid;
-    const int kofs = PART ? ((r * kw + sx) * Cin + cb * BKC) * 2 : j * (BKC * 2);
-#pragma unroll
-    for (int u = 0; u < AV; ++u) {
-      const bool in_img = col && ((vrow[u] >> r) & (vcol[u] >> sx) & 1u);
-      const int off = in_img ? a_offb[u] + tap_offb : (int)0x80000000;
-      ra_s[u] = __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0);
+  // ---- the K loop ----------------------------------------------------------
+  const uint32_t ring =
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + wave * 1024;
+  // load u of one chunk's L (A rows, then B rows) into the stage at LDS
+  // address dst; an offset with bit 31 set is out of range
+  auto load_part = [&](const WalkStep &e, uint32_t dst, int u) __attribute__((always_inline)) {
+    // PART: a lane's 8 channels of the chunk exist (channels past C_in in
+    // the last chunk of a tap read zero on both sides)
+    const int cb2 = PART ? e.kofs % (Cin * 2) : 0;   // bytes into the tap's channels
+    if (u < AV) {
+      const uint32_t out = orow[u] << e.rsh | ocol[u] << e.ssh;
+      uint32_t off = (uint32_t)(a_offb[u] + e.xofs) | (out & 0x80000000u);
+      if (PART && cb2 + cgA * 16 >= Cin * 2) off = 0x80000000u;
+      load_to_lds(xr, dst + u * (NW * 1024), (int)off, 0);
+    } else {
+      const bool colB = !PART || cb2 + cgB * 16 < Cin * 2;
+      load_to_lds(wr, dst + BM * ROW + (u - AV) * (NW * 1024),
+                  colB ? b_offb[u - AV] : (int)0x80000000, e.kofs);
     }
-#pragma unroll
-    for (int u = 0; u < BV; ++u)
-      rb_s[u] = __builtin_amdgcn_raw_buffer_load_b128(wr, col ? b_offb[u] : (int)0x80000000,
-                                                      valid ? kofs : 0, 0);
-  };
-  // every row a thread stores is rr mod 8 (RPU and BM are multiples of 8)
-  const int st_col = 16 * (cg ^ (rr & 7));
-  auto store_chunk = [&](int buf, const u32x4 (&ra_s)[AV], const u32x4 (&rb_s)[BV])
-                         __attribute__((always_inline)) {
-    char *s = stage(buf);
-#pragma unroll
-    for (int u = 0; u < AV; ++u)
-      *reinterpret_cast<u32x4 *>(s + (rr + RPU * u) * ROW + st_col) = ra_s[u];
-#pragma unroll
-    for (int u = 0; u < BV; ++u)
-      *reinterpret_cast<u32x4 *>(s + (BM + rr + RPU * u) * ROW + st_col) = rb_s[u];
   };
 
   f32x4 acc[WTM][WTN];
@@ -812,264 +872,250 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
     for (int j = 0; j < WTN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int g = lane >> 4, rl = lane & 15;
-  // operand rows of a lane are rl mod 16, so their swizzle is rl & 7
-  int ks_col[KS];
+  const int fB = (((rl >> 2) & 1) << 2) | (rl & 3);
+  int offA[2], offB[2];   // this lane's operand offsets of the two k-steps
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) ks_col[ks] = 16 * ((4 * ks + g) ^ (rl & 7));
-  auto compute = [&](int buf) __attribute__((always_inline)) {
-    const char *As = stage(buf) + (wm * WTM * 16 + rl) * ROW;
-    const char *Bs = stage(buf) + (BM + wn * WTN * 16 + rl) * ROW;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      u32x4 af[WTM], bfr[WTN];
-#pragma unroll
-      for (int tm = 0; tm < WTM; ++tm)
-        af[tm] = *reinterpret_cast<const u32x4 *>(As + tm * 16 * ROW + ks_col[ks]);
-#pragma unroll
-      for (int tn = 0; tn < WTN; ++tn)
-        bfr[tn] = *reinterpret_cast<const u32x4 *>(Bs + tn * 16 * ROW + ks_col[ks]);
-#pragma unroll
-      for (int tm = 0; tm < WTM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < WTN; ++tn) {
-          if constexpr (DT == SPAROA_BF16)
-            acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, af[tm]), __builtin_bit_cast(bf16x8, bfr[tn]),
-                acc[tm][tn], 0, 0, 0);
-          else
-            acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                __builtin_bit_cast(f16x8, af[tm]), __builtin_bit_cast(f16x8, bfr[tn]),
-                acc[tm][tn], 0, 0, 0);
-        }
-    }
-  };
-  // Chunk i lives in register slot i % PF until it is stored to LDS buffer
-  // i & 1 (one iteration ahead of its use); the slot is then refilled with
-  // chunk i + PF, so PF chunks of loads are always in flight.  The loop body
-  // is written out once per slot so every slot index is a constant and the
-  // ring stays in registers.
-  static_assert(PF >= 2 && PF <= 4, "register ring depth");
-  const int n = (int)count;
-  // dense walks (the dense kernel, and a dense-routed tile of the skip
-  // kernel) fill the list in dense order: no branch on the route inside the
-  // main loop
-  if (!SKIP || !use_list) {
-    if (!prefilled)
-      for (int i = tid; i < (int)count; i += NT) list[i] = pack_chunk((int)c_begin + i);
-    __syncthreads();
+  for (int ks = 0; ks < 2; ++ks) {
+    offA[ks] = (wm * WTM * 16 + rl) * ROW + 16 * ((4 * ks + g) ^ (rl & 7));
+    offB[ks] = (BM + wn * WTN * 16 + 16 * (rl >> 2) + (rl & 3)) * ROW + 16 * ((4 * ks + g) ^ fB);
   }
-  // (the list entry is the same in every lane: read it as a scalar, so the
-  // weight loads take it as their scalar offset -- an LDS value the
-  // compiler must treat as divergent made it wrap every weight load in a
-  // readfirstlane loop)
-  auto chunk_at = [&](int i) __attribute__((always_inline)) -> int {
-    return __builtin_amdgcn_readfirstlane(list[i]);
+  struct Operands {
+    u32x4 a[2][WTM], b[2][WTN];   // of a chunk's two k-steps
+  };
+  // read q of an operand set's R (k-step 0 first, channel rows before pixels)
+  constexpr int R = 2 * (WTM + WTN), MF = 2 * WTM * WTN, RSPAN = MF * 3 / 4;
+  auto read_part = [&](Operands &o, int slot, int q) __attribute__((always_inline)) {
+    const int ks = q / (WTM + WTN), v = q % (WTM + WTN);
+    const char *st = smem + slot * STAGE;
+    if (v < WTN)
+      o.b[ks][v] = *reinterpret_cast<const u32x4 *>(st + offB[ks] +
+                                                    (64 * (v >> 2) + 4 * (v & 3)) * ROW);
+    else
+      o.a[ks][v - WTN] = *reinterpret_cast<const u32x4 *>(st + offA[ks] + (v - WTN) * 16 * ROW);
+  };
+  auto multiply = [&](const Operands &o, int q) __attribute__((always_inline)) {
+    const int ks = q / (WTM * WTN), tm = q / WTN % WTM, b = q % WTN;
+    if constexpr (DT == SPAROA_BF16)
+      acc[tm][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          __builtin_bit_cast(bf16x8, o.b[ks][b]), __builtin_bit_cast(bf16x8, o.a[ks][tm]),
+          acc[tm][b], 0, 0, 0);
+    else
+      acc[tm][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+          __builtin_bit_cast(f16x8, o.b[ks][b]), __builtin_bit_cast(f16x8, o.a[ks][tm]),
+          acc[tm][b], 0, 0, 0);
+  };
+  const WalkGeom geom = walk_geom<2>(a);
+  const int n = __builtin_amdgcn_readfirstlane(count);
+  __syncthreads();   // the walk is written
+  // One step per chunk.  On entry the step's operands are in registers (or
+  // on their way from LDS).  After its barrier the next chunk's stage is
+  // complete and every wave has read this chunk's stage, which the loads of
+  // chunk i + S then refill between this chunk's MFMAs, while the next
+  // chunk's operands are read: a wave's LDS reads have a whole chunk of
+  // MFMAs to land.  The steady steps (STEADY: a next chunk and a refill
+  // exist) are written out for a whole turn of the ring and of the operand
+  // pair, with no branch and constant stages: at one or two waves per SIMD a
+  // step's scalar instructions are time.
+  uint32_t next;   // walk entry of the step's refill
+  auto step = [&](auto steady, Operands &cur, Operands &nxt, int slot, int i)
+                  __attribute__((always_inline)) {
+    constexpr bool STEADY = decltype(steady)::value;
+    const bool more = STEADY || i + 1 < n, refill = STEADY || i + S < n;
+    const uint32_t dst = ring + slot * STAGE;
+    const WalkStep e = walk_step(geom, next);
+    if (more) {
+      if constexpr (STEADY) wait_chunks<S - 2, L>(S - 2);
+      else wait_chunks<S - 2, L>(min(S - 2, n - 2 - i));
+      __builtin_amdgcn_s_waitcnt(kLgkmcnt0);   // this wave has read its stage
+      asm volatile("s_barrier" ::: "memory");
+      next = list[STEADY ? i + 1 + S : min(i + 1 + S, n - 1)];
+    }
+    const int nslot = slot == S - 1 ? 0 : slot + 1;
+#pragma unroll
+    for (int m = 0; m < MF; ++m) {
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(cur, m);
+      if (more) {
+#pragma unroll
+        for (int q = m * R / RSPAN; q < (m + 1) * R / RSPAN && q < R; ++q) read_part(nxt, nslot, q);
+      }
+      if (refill) {
+#pragma unroll
+        for (int u = m * L / MF; u < (m + 1) * L / MF; ++u) load_part(e, dst, u);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
   };
   if (n > 0) {
-    // chunk 0 alone first (every work-group starts at once: a deep prologue
-    // would queue each one's first chunk behind all the others' prefetch)
-    // (chunks past the last are not loaded: short K -- a 1x1 conv over 64
-    // channels is one chunk -- would otherwise re-read its chunks PF times)
-    load_chunk(chunk_at(0), ra[0], rb[0], true);
-    store_chunk(0, ra[0], rb[0]);
-    load_chunk(chunk_at(min(1, n - 1)), ra[1], rb[1], 1 < n);
-    if constexpr (PF > 2)
-      load_chunk(chunk_at(min(2, n - 1)), ra[PF > 2 ? 2 : 0], rb[PF > 2 ? 2 : 0], 2 < n);
-    if constexpr (PF > 3)
-      load_chunk(chunk_at(min(3, n - 1)), ra[PF > 3 ? 3 : 0], rb[PF > 3 ? 3 : 0], 3 < n);
-    load_chunk(chunk_at(min(PF, n - 1)), ra[0], rb[0], PF < n);
-    __syncthreads();
-  // Steady state: groups of PF straight-line steps (no branch inside a step,
-  // so the compiler's load counters stay exact and PF chunks stay in flight);
-  // the refill past the end re-reads the last chunk.  The last group runs
-  // the guarded form.
-#define SPAROA_IG_STEP(D, GUARD)                                                   \
-  {                                                                                \
-    constexpr int sn = ((D) + 1) % PF;                                             \
-    const int i = i0 + (D);                                                        \
-    if (!(GUARD) || i < n) {                                                       \
-      const int jn = chunk_at(min(i + 1 + PF, n - 1)); /* read before the MFMAs */ \
-      compute(i & 1);                                                              \
-      if (!(GUARD) || i + 1 < n) store_chunk((i + 1) & 1, ra[sn], rb[sn]); \
-      if (!(GUARD) || i + 1 + PF < n) load_chunk(jn, ra[sn], rb[sn], true);      \
-      __syncthreads();                                                             \
-    }                                                                              \
-  }
-    int i0 = 0;
-    for (; i0 + PF < n; i0 += PF) {
-      SPAROA_IG_STEP(0, false)
-      SPAROA_IG_STEP(1, false)
-      if constexpr (PF > 2) SPAROA_IG_STEP(2, false)
-      if constexpr (PF > 3) SPAROA_IG_STEP(3, false)
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      if (s < n) {
+        const WalkStep e = walk_step(geom, list[s]);
+#pragma unroll
+        for (int u = 0; u < L; ++u) load_part(e, ring + s * STAGE, u);
+      }
+    wait_chunks<S - 1, L>(min(S - 1, n - 1));
+    asm volatile("s_barrier" ::: "memory");
+    Operands p, q;
+#pragma unroll
+    for (int r = 0; r < R; ++r) read_part(p, 0, r);
+    next = list[min(S, n - 1)];
+    constexpr int U = S % 2 ? 2 * S : S;   // a turn of the ring and of (p, q)
+    int i = 0;
+    // (the last step of a turn prefetches the walk entry of chunk i + U + S)
+    for (; i + U + S < n; i += U) {
+#pragma unroll
+      for (int d = 0; d < U; ++d)
+        step(std::true_type{}, d % 2 ? q : p, d % 2 ? p : q, d % S, i + d);
     }
-    for (; i0 < n; i0 += PF) {
-      SPAROA_IG_STEP(0, true)
-      SPAROA_IG_STEP(1, true)
-      if constexpr (PF > 2) SPAROA_IG_STEP(2, true)
-      if constexpr (PF > 3) SPAROA_IG_STEP(3, true)
+    for (; i < n; i += U) {
+#pragma unroll
+      for (int d = 0; d < U; ++d)
+        if (i + d < n) step(std::false_type{}, d % 2 ? q : p, d % 2 ? p : q, d % S, i + d);
     }
-#undef SPAROA_IG_STEP
   }
 
-  // ---- epilogue: the fp32 tile goes through LDS (a lane holds rows
-  // 4*(lane/16) + v, column lane % 16 of each MFMA block), then each thread
-  // finishes 8 consecutive columns of a row: bias and residual as 16-byte
-  // loads, one 16-byte store.
-  using raw = typename E::raw;
-  float *ct = reinterpret_cast<float *>(smem_raw);
-  __syncthreads();
-#pragma unroll
-  for (int tm = 0; tm < WTM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < WTN; ++tn)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        ct[(wm * WTM * 16 + tm * 16 + 4 * g + v) * CS + wn * WTN * 16 + tn * 16 + rl] =
-            acc[tm][tn][v];
-  __syncthreads();
-  constexpr int C8 = BN / 8;
-  constexpr int EIT = BM * C8 / NT;   // epilogue rows per thread
-  static_assert(BM * C8 % NT == 0 && NT % C8 == 0, "epilogue mapping");
-  const bool vec_n = a.N % 8 == 0;
-  // A thread's 8 columns are the same in every epilogue row (NT is a
-  // multiple of C8): its bias vector is loaded once, and the residual
-  // vectors of all its rows are requested before its first store (a load
-  // issued behind stores waits for them here, which serialised the rows).
-  const int c_t = (tid % C8) * 8;
-  const bool vec_t = vec_n && a.split == 1 && n0 + c_t < a.N;
-  using raw_t = typename E::raw;
-  uint4 bias_q = {0u, 0u, 0u, 0u};
-  if (a.bias && vec_t)
-    bias_q = *reinterpret_cast<const uint4 *>(reinterpret_cast<const raw_t *>(a.bias) + n0 + c_t);
-  uint4 res_q[EIT];
-#pragma unroll
-  for (int it = 0; it < EIT; ++it) {
-    const int64_t row = m0 + (tid + it * NT) / C8;
-    res_q[it] = uint4{0u, 0u, 0u, 0u};
-    if (a.residual && vec_t && row < a.M)
-      res_q[it] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const raw_t *>(a.residual) +
-                                                   row * a.N + n0 + c_t);
-  }
-  // Output measurement (host: no split, N % 64 == 0, and N % BN == 0 for
-  // wider tiles): each 8 consecutive lanes of a tile row hold one bitmap byte
-  // (8 channel blocks of 8); every lane stays in the loop for the ballot.
+  // ---- epilogue, from registers: a lane holds channels 16 g + [0, 16) of
+  // each 64-channel group of pixel rl of its WTM pixel blocks -- two 16-byte
+  // vectors of bias, residual and output (four lanes of a pixel write 128
+  // consecutive bytes).  The residual vectors are requested before the first
+  // store (a load issued behind stores waits for them).
+  const bool vec_n = N % 8 == 0;
+  const int mw = m0 + wm * WTM * 16 + rl, nw = n0 + wn * WTN * 16 + 16 * g;
   uint32_t om_zeros = 0, om_nz = 0;
+  if (a.split > 1) {
 #pragma unroll
-  for (int it = 0; it < EIT; ++it) {
-    const int q = tid + it * NT;
-    const int r = q / C8, c = (q % C8) * 8;
-    const int64_t row = m0 + r, col = n0 + c;
-    if (om) {
-      const bool valid = row < a.M;
-      uint32_t nzb = 0;
-      if (valid) {
+    for (int tm = 0; tm < WTM; ++tm) {
+      const int row = mw + 16 * tm;
+      if (row >= M) continue;
+#pragma unroll
+      for (int q = 0; q < NG; ++q) {
+        const int col = nw + 64 * q;
+        float *dst = a.partial + ((int64_t)zsplit * M + row) * N + col;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const f32x4 v = acc[tm][4 * q + b];
+          if (vec_n) {
+            if (col + 4 * b < N) *reinterpret_cast<f32x4 *>(dst + 4 * b) = v;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (col + 4 * b + e < N) dst[4 * b + e] = v[e];
+          }
+        }
+      }
+    }
+    return;
+  }
+  const raw *bias = reinterpret_cast<const raw *>(a.bias);
+  const raw *res = reinterpret_cast<const raw *>(a.residual);
+  raw *y = reinterpret_cast<raw *>(a.y);
+  if (!vec_n) {
+#pragma unroll
+    for (int tm = 0; tm < WTM; ++tm) {
+      const int row = mw + 16 * tm;
+      if (row >= M) continue;
+#pragma unroll
+      for (int b = 0; b < WTN; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int col = nw + 64 * (b >> 2) + 4 * (b & 3) + e;
+          if (col >= N) continue;
+          float v = acc[tm][b][e];
+          if (bias) v += E::to_f32(bias[col]);
+          if (res) v += E::to_f32(res[(int64_t)row * N + col]);
+          y[(int64_t)row * N + col] = E::from_f32(apply_act(v, a.act));
+        }
+    }
+    return;   // (N % 64 == 0 whenever the output is measured)
+  }
+  uint4 bias_q[NG][2], res_q[WTM][NG][2];
+#pragma unroll
+  for (int q = 0; q < NG; ++q)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int col = nw + 64 * q + 8 * h;
+      bias_q[q][h] = uint4{0u, 0u, 0u, 0u};
+      if (bias && col < N) bias_q[q][h] = *reinterpret_cast<const uint4 *>(bias + col);
+    }
+  if (res) {
+#pragma unroll
+    for (int tm = 0; tm < WTM; ++tm)
+#pragma unroll
+      for (int q = 0; q < NG; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int row = mw + 16 * tm, col = nw + 64 * q + 8 * h;
+          res_q[tm][q][h] = uint4{0u, 0u, 0u, 0u};
+          if (row < M && col < N)
+            res_q[tm][q][h] =
+                *reinterpret_cast<const uint4 *>(res + (int64_t)row * N + col);
+        }
+  }
+  // output measurement (N % 64 == 0): the eight (1, 8) blocks of a pixel's
+  // 64-channel group are one bitmap byte, met by two ballots
+  const int mbytes = om && a.om_mask ? (int)(4 * (((int64_t)M * (N / 8) + 31) / 32)) : 0;
+#pragma unroll
+  for (int tm = 0; tm < WTM; ++tm) {
+    const int row = mw + 16 * tm;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      uint32_t nzb[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int col = nw + 64 * q + 8 * h;
+        const bool valid = row < M && col < N;
         float o[8];
-        const float4 lo = *reinterpret_cast<const float4 *>(&ct[r * CS + c]);
-        const float4 hi = *reinterpret_cast<const float4 *>(&ct[r * CS + c + 4]);
-        o[0] = lo.x; o[1] = lo.y; o[2] = lo.z; o[3] = lo.w;
-        o[4] = hi.x; o[5] = hi.y; o[6] = hi.z; o[7] = hi.w;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = acc[tm][4 * q + 2 * h + (e >> 2)][e & 3];
         raw t[8], out[8];
-        if (a.bias) {
-          __builtin_memcpy(t, &bias_q, 16);
+        if (bias) {
+          __builtin_memcpy(t, &bias_q[q][h], 16);
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] += E::to_f32(t[e]);
         }
-        if (a.residual) {
-          __builtin_memcpy(t, &res_q[it], 16);
+        if (res) {
+          __builtin_memcpy(t, &res_q[tm][q][h], 16);
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] += E::to_f32(t[e]);
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          out[e] = E::from_f32(apply_act(o[e], a.act));
-          const bool z = (out[e] & 0x7FFFu) == 0u;
-          om_zeros += z ? 1u : 0u;
-          nzb |= z ? 0u : 1u;
-        }
+        for (int e = 0; e < 8; ++e) out[e] = E::from_f32(apply_act(o[e], a.act));
         uint4 q4;
         __builtin_memcpy(&q4, out, 16);
-        *reinterpret_cast<uint4 *>(reinterpret_cast<raw *>(a.y) + row * a.N + col) = q4;
-      }
-      om_nz += nzb;
-      const uint64_t bal = __ballot(nzb != 0u);
-      // the tile's bitmap bytes (8 channel blocks of 8 per byte) meet in LDS
-      // and each row's BN / 64 bytes leave as one store below
-      if ((lane & 7) == 0) ombytes[r * (BN / 64) + c / 64] = valid ? (uint8_t)(bal >> (lane & ~7)) : 0;
-      continue;
-    }
-    if (row >= a.M || col >= a.N) continue;
-    float o[8];
-    {
-      const float4 lo = *reinterpret_cast<const float4 *>(&ct[r * CS + c]);
-      const float4 hi = *reinterpret_cast<const float4 *>(&ct[r * CS + c + 4]);
-      o[0] = lo.x; o[1] = lo.y; o[2] = lo.z; o[3] = lo.w;
-      o[4] = hi.x; o[5] = hi.y; o[6] = hi.z; o[7] = hi.w;
-    }
-    const int ne = (int)min((int64_t)8, a.N - col);
-    if (a.split > 1) {
-      float *dst = a.partial + (zsplit * a.M + row) * a.N + col;
-      if (vec_n) {
-        *reinterpret_cast<float4 *>(dst) = make_float4(o[0], o[1], o[2], o[3]);
-        *reinterpret_cast<float4 *>(dst + 4) = make_float4(o[4], o[5], o[6], o[7]);
-      } else {
-        for (int e = 0; e < ne; ++e) dst[e] = o[e];
-      }
-      continue;
-    }
-    raw *dst = reinterpret_cast<raw *>(a.y) + row * a.N + col;
-    if (vec_n) {
-      raw bv[8], rv[8], out[8];
-      if (a.bias) {
-        __builtin_memcpy(bv, &bias_q, 16);
+        if (valid) *reinterpret_cast<uint4 *>(y + (int64_t)row * N + col) = q4;
+        nzb[h] = 0;
+        if (om) {
+          uint32_t any = 0, zeros = 0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] += E::to_f32(bv[e]);
+          for (int e = 0; e < 8; ++e) {
+            // zero test in integer arithmetic (m - 1 wraps to bit 31 iff m == 0)
+            const uint32_t mag = (uint32_t)out[e] & E::mag_mask;
+            zeros += (mag - 1u) >> 31;
+            any |= mag;
+          }
+          om_zeros += valid ? zeros : 0u;
+          nzb[h] = valid && any ? 1u : 0u;
+          om_nz += nzb[h];
+        }
       }
-      if (a.residual) {
-        __builtin_memcpy(rv, &res_q[it], 16);
+      if (mbytes) {
+        const uint64_t b0 = __ballot(nzb[0] != 0u), b1 = __ballot(nzb[1] != 0u);
+        // rows past M still clear their bytes when they lie inside the
+        // bitmap's last word (bits past the last block are 0)
+        const int byte = row * (N / 64) + (nw - 16 * g) / 64 + q;
+        if (g == 0 && nw + 64 * q < N && byte < mbytes) {
+          uint32_t v = 0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] += E::to_f32(rv[e]);
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) out[e] = E::from_f32(apply_act(o[e], a.act));
-      uint4 q4;
-      __builtin_memcpy(&q4, out, 16);
-      *reinterpret_cast<uint4 *>(dst) = q4;
-    } else {
-      for (int e = 0; e < ne; ++e) {
-        float v = o[e];
-        if (a.bias) v += E::to_f32(reinterpret_cast<const raw *>(a.bias)[col + e]);
-        if (a.residual) v += E::to_f32(reinterpret_cast<const raw *>(a.residual)[row * a.N + col + e]);
-        dst[e] = E::from_f32(apply_act(v, a.act));
+          for (int p = 0; p < 4; ++p)
+            v |= ((uint32_t)(b0 >> (rl + 16 * p)) & 1u) << (2 * p) |
+                 ((uint32_t)(b1 >> (rl + 16 * p)) & 1u) << (2 * p + 1);
+          reinterpret_cast<uint8_t *>(a.om_mask)[byte] = (uint8_t)v;
+        }
       }
     }
   }
-  if (om) {
-    __syncthreads();
-    // rows past M still clear their bytes when they lie inside the bitmap's
-    // last word (bits past the last block are 0)
-    const int64_t mbytes = a.om_mask ? 4 * ((a.M * (a.N / 8) + 31) / 32) : 0;   // null: counts only
-    for (int r = tid; r < BM; r += NT) {
-      const int64_t row = m0 + r, byte = row * (a.N / 64) + n0 / 64;
-      if (byte >= mbytes) continue;   // (BN / 64 bytes of a row lie in one word)
-      if constexpr (BN == 256) {      // n0 / 64 and N / 64 multiples of 4: 4-byte aligned
-        const uint32_t v = (uint32_t)ombytes[4 * r] | ((uint32_t)ombytes[4 * r + 1] << 8) |
-                           ((uint32_t)ombytes[4 * r + 2] << 16) |
-                           ((uint32_t)ombytes[4 * r + 3] << 24);
-        *reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(a.om_mask) + byte) = v;
-      } else if constexpr (BN == 128) {  // n0 / 64 and N / 64 even: 2-byte aligned
-        const uint16_t v = (uint16_t)(ombytes[2 * r] | (ombytes[2 * r + 1] << 8));
-        *reinterpret_cast<uint16_t *>(reinterpret_cast<uint8_t *>(a.om_mask) + byte) = v;
-      } else {
-        reinterpret_cast<uint8_t *>(a.om_mask)[byte] = ombytes[r];
-      }
-    }
-  }
-  return make_uint2(om_zeros, om_nz);
-  };
-  // (one tile per work-group; the lambda form measured fewer scalar-register
-  // spills than straight-line code)
-  const uint2 t = tile_body((int)blockIdx.x);
-  if (om) om_commit(t.x, t.y, a.om_counts, a.om_words, blockIdx.x, gridDim.x);
+  if (om) om_commit(om_zeros, om_nz, a.om_counts, a.om_words, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1334,33 +1380,33 @@ __global__ __launch_bounds__(256) void conv_small_c_kernel(SmallCArgs a) {
   if (a.om_counts) om_commit(om_zeros, om_nz, a.om_counts, a.om_words, blockIdx.x, gridDim.x);
 }
 
-template <int DT, int WGM, int WGN, int WTM, int WTN, int PF, int KS, bool SKIP, bool PART>
+template <int DT, int WGM, int WGN, int WTM, int WTN, int S, bool PART>
 void launch_ig(dim3 grid, hipStream_t st, const GemmArgs &a) {
-  hipLaunchKernelGGL((igemm_kernel<DT, WGM, WGN, WTM, WTN, PF, KS, SKIP, PART>), grid,
+  hipLaunchKernelGGL((igemm_kernel<DT, WGM, WGN, WTM, WTN, S, PART>), grid,
                      dim3(64 * WGM * WGN), 0, st, a);
 }
 
-// Tile configurations of the second-generation kernel (BM x BN) and the
-// chunks each keeps in flight in registers.
-enum IgCfg { kIg128x64 = 1, kIg64x64, kIg128x128, kIg128x256 };
+// Tile configurations of the second-generation kernel (BM x BN); 64 x 128
+// with a ring of 3 stages (two work-groups per CU) or of 5 (Deep: one).
+enum IgCfg { kIg64x64 = 1, kIg64x128, kIg64x128Deep, kIg128x64, kIg128x128, kIg128x128Many, kIg128x256 };
 
-// 64-channel chunks: two MFMA k-steps per barrier (four measured slower:
-// more LDS and registers per work-group for the same latency per step).
-template <int DT, bool SKIP>
-bool dispatch_ig(int cfg, int kchunk, bool part, dim3 grid, hipStream_t st, const GemmArgs &a) {
-  if (kchunk != kBK2) return false;
+template <int DT>
+bool dispatch_ig(int cfg, bool part, dim3 grid, hipStream_t st, const GemmArgs &a) {
   if (part) {   // partial chunks: the two tiles the chooser takes for them
     switch (cfg) {
-      case kIg128x64: launch_ig<DT, 2, 2, 4, 2, 4, 2, SKIP, true>(grid, st, a); return true;
-      case kIg64x64: launch_ig<DT, 2, 2, 2, 2, 4, 2, SKIP, true>(grid, st, a); return true;
+      case kIg64x64: launch_ig<DT, 4, 1, 1, 4, 4, true>(grid, st, a); return true;
+      case kIg128x64: launch_ig<DT, 8, 1, 1, 4, 3, true>(grid, st, a); return true;
     }
     return false;
   }
   switch (cfg) {
-    case kIg128x64: launch_ig<DT, 2, 2, 4, 2, 4, 2, SKIP, false>(grid, st, a); return true;
-    case kIg64x64: launch_ig<DT, 2, 2, 2, 2, 4, 2, SKIP, false>(grid, st, a); return true;
-    case kIg128x128: launch_ig<DT, 2, 2, 4, 4, 3, 2, SKIP, false>(grid, st, a); return true;
-    case kIg128x256: launch_ig<DT, 2, 4, 4, 4, 3, 2, SKIP, false>(grid, st, a); return true;
+    case kIg64x64: launch_ig<DT, 4, 1, 1, 4, 4, false>(grid, st, a); return true;
+    case kIg64x128: launch_ig<DT, 4, 2, 1, 4, 3, false>(grid, st, a); return true;
+    case kIg64x128Deep: launch_ig<DT, 4, 2, 1, 4, 5, false>(grid, st, a); return true;
+    case kIg128x64: launch_ig<DT, 8, 1, 1, 4, 3, false>(grid, st, a); return true;
+    case kIg128x128: launch_ig<DT, 4, 2, 2, 4, 3, false>(grid, st, a); return true;
+    case kIg128x128Many: launch_ig<DT, 2, 2, 4, 4, 2, false>(grid, st, a); return true;
+    case kIg128x256: launch_ig<DT, 2, 4, 4, 4, 3, false>(grid, st, a); return true;
   }
   return false;
 }
@@ -1569,40 +1615,63 @@ bool ig_eligible(const sparoa_conv_desc &d) {
          d.kh * d.kw * (d.c_in / 8) <= (int64_t)kMaxVecWords * 32;
 }
 
-// Tile of the second-generation kernel: the largest tile that still gives
-// every CU a work-group, else the smallest with split-K.
+// Column groups of the tile walk: the 8 XCDs' L2s read x once per group and
+// the weights once per XCD of a group, so of 1, 2, 4 and 8 groups the one
+// with the fewest bytes.
+int64_t ig_column_groups(int64_t ntn, int64_t x_bytes, int64_t w_bytes) {
+  int64_t best = 1;
+  for (int64_t g = 2; g <= 8 && g <= ntn; g *= 2)
+    if (x_bytes * g + w_bytes * (8 / g) < x_bytes * best + w_bytes * (8 / best)) best = g;
+  return best;
+}
+
+// Tile of the second-generation kernel.  128 pixels where 128 x 64 tiles fill
+// the chip, else 64.  Then the widest tile that still gives about one per CU:
+// what bounds these kernels is the L2's delivery into LDS (17 - 20 TB/s over
+// the chip, whatever the depth of the ring), and a tile of BM x BN takes
+// 128 (BM + BN) bytes per chunk for BM BN products.  Measured (fp16, residual,
+// one tile column of each row; M x N x K in us):
+//   64 rows:  64 x 64 up to 256 tiles (2048 x 512 x 1024 9.6, 64 x 128 10.8),
+//     else 64 x 128 (6272 x 256 x 256 7.0, 64 x 64 7.3), its deep ring from
+//     32 chunks (6272 x 256 x 2304 16.2, 3 stages 17.4; x 1024 11.4, 11.3);
+//   128 rows: 128 x 256 where it gives 192 to 256 tiles, or more of them and
+//     12 chunks (25088 x 256 x 1024 23.1, 128 x 128 26.7; 50176 x 256 x 2304
+//     65.2 and 72.2, x 576 32.6 and 31.6);
+//     128 x 128 for up to 256 tiles of it (25088 x 128 x 1152 12.3, 128 x 64
+//     12.6; x 2304 22.4 and 25.1), above that its form of four waves, two
+//     work-groups per CU (50176 x 128 x 576 18.5, eight waves 22.9); 128 x 64
+//     elsewhere.
+// (partial chunks, C_in % 64 != 0: 64 channels wide only)
 GemmTileChoice ig_choose(const Shape &s, int64_t c_in) {
   auto tiles = [&](int bm, int bn) { return cdiv(s.M, bm) * cdiv(s.N, bn); };
   GemmTileChoice t;
   t.kchunk = kBK2;
-  const bool one_tap = s.K == c_in;  // 1 x 1 kernel: a plain GEMM over channels
-  // 128 x 64 (waves of 64 x 32, two work-groups per CU) wherever it fills
-  // the chip: it beat 128 x 128 (one work-group per CU) by 10 - 25% on 3x3
-  // convs at N = 32 (638 vs 506 TFLOP/s at 256 channels, 56 x 56)
-  // 128 x 128 (waves of 64 x 64: half the LDS reads per MFMA, two
-  // work-groups per CU) where it still gives each CU several tiles: 19-23 %
-  // faster on 3x3 convs with 256-512 channels at 56 x 56, N = 32; with fewer
-  // tiles the chip runs part-empty and 128 x 64 wins
-  // 128 x 256 (eight waves of 64 x 64, one work-group per CU) for 1 x 1
-  // kernels with enough tiles: each A row is gathered once per 256 output
-  // channels instead of 128; 7 - 13 % faster on 1 x 1 convs and GEMMs with
-  // N >= 1024 (FFN 2048 x 768 -> 3072: 28.2 -> 25.8 us), 2 - 9 % slower on
-  // 3 x 3 convs with 256-512 channels, which keep 128 x 128
-  // (partial chunks, C_in % 64 != 0: 128 x 64 or 64 x 64 only)
   const bool whole = c_in % t.kchunk == 0;
-  if (whole && one_tap && s.N % 256 == 0 && tiles(128, 256) >= 192) {
-    t.cfg = kIg128x256; t.bm = 128; t.bn = 256;
-  } else if (whole && s.N % 128 == 0 && tiles(128, 128) >= 384) {
-    t.cfg = kIg128x128; t.bm = 128; t.bn = 128;
-  } else if (tiles(128, 64) >= 240) {
-    t.cfg = kIg128x64; t.bm = 128; t.bn = 64;
+  const int64_t chunks = (s.K / c_in) * cdiv(c_in, t.kchunk);
+  // BN-wide tiles waste at most an eighth of their columns
+  auto wide = [&](int bn) { return whole && cdiv(s.N, bn) * bn - s.N <= s.N / 8; };
+  if (tiles(128, 64) >= 240) {
+    t.bm = 128;
+    const int64_t n256 = tiles(128, 256), n128 = tiles(128, 128);
+    if (wide(256) && n256 >= 192 && (n256 <= 256 || chunks >= 12)) {
+      t.cfg = kIg128x256; t.bn = 256;
+    } else if (wide(128) && n128 >= 160) {
+      t.cfg = n128 <= 256 ? kIg128x128 : kIg128x128Many; t.bn = 128;
+    } else {
+      t.cfg = kIg128x64; t.bn = 64;
+    }
   } else {
-    t.cfg = kIg64x64; t.bm = 64; t.bn = 64;
+    t.bm = 64;
+    if (wide(128) && tiles(64, 64) > 256) {
+      t.cfg = chunks >= 32 ? kIg64x128Deep : kIg64x128; t.bn = 128;
+    } else {
+      t.cfg = kIg64x64; t.bn = 64;
+    }
   }
   // chunks: whole or partial 64-channel blocks of each tap
-  const int64_t tl = tiles(t.bm, t.bn), nchunks = (s.K / c_in) * cdiv(c_in, t.kchunk);
+  const int64_t tl = tiles(t.bm, 64), nchunks = chunks;
   int64_t split = 1;
-  if (tl < 192) {
+  if (tl < 192) {   // (64 x 64 tiles: the wider ones are taken from 192 on)
     // about one work-group per CU: more splits cost more partial traffic than
     // they gain (FC 64 x 4096 x 4096: split 4 15.1 us, split 8 17.8 us)
     split = cdiv(256, tl);
@@ -1734,7 +1803,7 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
   a.residual = static_cast<const char *>(residual);
   a.y = static_cast<char *>(y);
   a.partial = static_cast<float *>(ws);
-  a.mask = mask;
+  a.mask = skip ? mask : nullptr;
   a.executed = reinterpret_cast<unsigned long long *>(skip ? executed : nullptr);
   a.M = s.M; a.N = s.N; a.K = s.K;
   a.H = d.h; a.W = d.w; a.Cin = d.c_in; a.Ho = s.ho; a.Wo = s.wo; a.Kw = d.kw;
@@ -1753,6 +1822,7 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
   a.chunks_per_split = cdiv(nchunks, t.split_k);
   a.act = act;
   a.route = route ? *route : DeviceRoute{nullptr, 0.0, 0, 0, nullptr};
+  if (!skip) a.route.counts = nullptr;   // no skip form to route to
   const int64_t gz = cdiv(nchunks, a.chunks_per_split);
   a.split = (int)gz;
   // the epilogue measures y when it writes y; with split-K the reduction does
@@ -1785,10 +1855,17 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
     if (ntmn * gz >= (int64_t)1 << 24)
       return fail(SPAROA_ERR_UNSUPPORTED, "GEMM: 2^24 tiles or more");
     grid = dim3((unsigned)(ntmn * gz));
+    const int64_t gw = cdiv(ntn, ig_column_groups(ntn, a.x_bytes, a.w_bytes));
+    const int64_t gt = ntmn / ntn * gw, lastw = ntn - (cdiv(ntn, gw) - 1) * gw;
     a.ntn32 = (int)ntn;
     a.ntmn32 = (int)ntmn;
-    a.inv_ntn = 1.0f / (float)ntn;
+    a.gw32 = (int)gw;
+    a.gt32 = (int)gt;
+    a.lastw32 = (int)lastw;
     a.inv_ntmn = 1.0f / (float)ntmn;
+    a.inv_gt = 1.0f / (float)gt;
+    a.inv_gw = 1.0f / (float)gw;
+    a.inv_lastw = 1.0f / (float)lastw;
     a.cpt32 = (int)cdiv(d.c_in, t.kchunk);
     a.inv_cpt = 1.0f / (float)a.cpt32;
   }
@@ -1797,12 +1874,10 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
   if (t.cfg) {
     switch (d.dtype) {
       case SPAROA_BF16:
-        ok = skip ? dispatch_ig<SPAROA_BF16, true>(t.cfg, t.kchunk, part, grid, stream, a)
-                  : dispatch_ig<SPAROA_BF16, false>(t.cfg, t.kchunk, part, grid, stream, a);
+        ok = dispatch_ig<SPAROA_BF16>(t.cfg, part, grid, stream, a);
         break;
       case SPAROA_F16:
-        ok = skip ? dispatch_ig<SPAROA_F16, true>(t.cfg, t.kchunk, part, grid, stream, a)
-                  : dispatch_ig<SPAROA_F16, false>(t.cfg, t.kchunk, part, grid, stream, a);
+        ok = dispatch_ig<SPAROA_F16>(t.cfg, part, grid, stream, a);
         break;
       default: break;
     }
