@@ -1068,7 +1068,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
         float o[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] = acc[tm][4 * q + 2 * h + (e >> 2)][e & 3];
-        raw t[8], out[8];
+        raw t[8];
         if (bias) {
           __builtin_memcpy(t, &bias_q[q][h], 16);
 #pragma unroll
@@ -1079,23 +1079,18 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] += E::to_f32(t[e]);
         }
+        uint32_t w[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = E::from_f32(apply_act(o[e], a.act));
+        for (int e = 0; e < 4; ++e)
+          w[e] = E::pack2(apply_act(o[2 * e], a.act), apply_act(o[2 * e + 1], a.act));
         uint4 q4;
-        __builtin_memcpy(&q4, out, 16);
+        __builtin_memcpy(&q4, w, 16);
         if (valid) *reinterpret_cast<uint4 *>(y + (int64_t)row * N + col) = q4;
         nzb[h] = 0;
         if (om) {
-          uint32_t any = 0, zeros = 0;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            // zero test in integer arithmetic (m - 1 wraps to bit 31 iff m == 0)
-            const uint32_t mag = (uint32_t)out[e] & E::mag_mask;
-            zeros += (mag - 1u) >> 31;
-            any |= mag;
-          }
-          om_zeros += valid ? zeros : 0u;
-          nzb[h] = valid && any ? 1u : 0u;
+          const uint32_t nz = nonzeros16<4>(w);
+          om_zeros += valid ? 8u - nz : 0u;
+          nzb[h] = valid && nz ? 1u : 0u;
           om_nz += nzb[h];
         }
       }
@@ -1122,38 +1117,44 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
 // Direct MFMA conv for inputs with at most 4 channels (image stems: ResNet's
 // 7x7/2 and MobileNetV2's 3x3/2 over RGB), where the implicit GEMM's 8- or
 // 64-channel K chunks would be mostly padding and its gathers scalar.  A
-// work-group computes one output row (all Wo pixels, all C_out <= 64
-// channels).  It stages the kh input rows the row needs, zero-padded on both
-// sides, in LDS as [kh][PW][4] (channels padded to 4 with zeros), so K is
-// laid out as (kernel row r, tap pair j, tap parity, channel): an 8-element
-// block of K is two taps x 4 channels, contiguous and 8-byte aligned in the
-// patch.  K = kh * ceil(kw/2) blocks, four per v_mfma_f32_16x16x32 k-step;
-// a tap past kw (odd kw) and blocks past the last kernel row read zero.  The
-// B operands (weights, zero-padded the same way) stay in registers.  Waves
-// split C_out into 16-channel column blocks and the Wo pixels into 16-pixel
-// row blocks.  Skip form: an MFMA whose A operand is zero in all 64 lanes is
-// not issued (it would add exact zeros), so the skip output equals the dense
-// output bit for bit; executed_blocks counts the issued (row block, k-step)
-// pairs.  The fp32 tile goes through LDS to 16-byte stores with bias,
-// residual and activation; each thread's 8 output channels of a pixel are one
-// (1, 8) block of the output, so the epilogue also counts zeros and nonzero
-// blocks when asked (counts-only measurement of y, one ticketed commit per
-// work-group).
+// work-group computes `rw` output rows of one image (all Wo pixels, all
+// C_out <= 64 channels).  It stages the input rows they need, zero-padded on
+// both sides, in LDS as [row][PWP][4] (channels padded to 4 with zeros), so K
+// is laid out as (kernel row r, tap pair j, tap parity, channel): an
+// 8-element block of K is two taps x 4 channels, contiguous and 8-byte
+// aligned in the patch.  K = kh * ceil(kw/2) blocks, four per
+// v_mfma_f32_16x16x32 k-step; a tap past kw (odd kw) and blocks past the last
+// kernel row read zero.  The weights, laid out the same way, pass through LDS
+// once into registers, where a wave keeps all C_out channels: a 16-pixel
+// block's patch operands are read once for all of them.  Each wave walks
+// whole 16-pixel blocks of a row; the MFMA's rows are channels, so a lane
+// ends with 4 NB consecutive channels of its pixel and finishes them from
+// registers.  Bound by its output stores (51 MB on ResNet-50's at N = 32);
+// one work-group per row with a wave per 16 channels, the patch re-read for
+// each and the tile staged in LDS took 75 us there, this form 29 us (at N = 8
+// 24 -> 12.5 us, at N = 1 13 -> 6.7 us; more waves per CU spilled: 37 us).
+// Skip form: MFMAs whose patch operand is zero in all 64 lanes are not issued
+// (they would add exact zeros), so the skip output equals the dense output
+// bit for bit; executed_blocks counts the (row block, k-step) pairs issued.
+// Output measurement: a lane's 8 channels are one (1, 8) block of the output,
+// so the epilogue also counts zeros and nonzero blocks when asked
+// (counts-only measurement of y, one ticketed commit per work-group).
 constexpr int kScMaxKSteps = 8;
 constexpr int kScMaxRB = 8;            // Wo <= 128
-constexpr int kScPatchBytes = 48 * 1024;  // LDS bound of the eligible shapes
+constexpr int kScPatchBytes = 48 * 1024;  // bound of the eligible shapes (small_c_eligible)
+constexpr int kScLdsBytes = 64 * 1024;    // LDS of a work-group
 
 struct SmallCArgs {
   const char *x, *w, *bias, *residual;
   char *y;
   unsigned long long *executed;
-  int N, H, W, C, Ho, Wo, Cout, kh, kw, sh, sw, ph, pw;
-  int PW, PWP, bpr, ksteps, act;   // PWP = PW + 1: patch row pitch in pixels
-  int raw_elems, w_elems;  // LDS elements of the raw rows and the weights (each % 8 == 0)
-  int c_w;                 // weight elements (Cout * kh * kw * C)
-  int region_off;          // LDS byte offset of the weights / raw rows / tile region
-  float inv_bpr, inv_rv, inv_rowe;   // 1 / bpr, 1 / (W*C/8), 1 / (W*C), rounded once
-  int vec;                 // rows and weights are whole 16-byte vectors
+  int H, W, C, Ho, Wo, Cout, kh, kw, sh, sw, ph, pw;
+  int PWP, bpr, act;
+  int pair;                // an input row is whole dwords (W C even)
+  int rw, groups;          // output rows per work-group (1, 2 or 4), work-groups per image
+  int prows;               // patch rows: (rw - 1) sh + kh
+  int patch_off;           // LDS byte offset of the patch (0: it replaces the weights)
+  float inv_bpr, inv_pwp;  // rounded once
   int mode;  // 0 dense, 1 skip, 2 device route
   DeviceRoute route;
   // counts-only output measurement at block (1 pixel, 8 channels): non-null
@@ -1162,220 +1163,244 @@ struct SmallCArgs {
   unsigned long long *om_words;
 };
 
-template <int DT, int KS>
-__global__ __launch_bounds__(256) void conv_small_c_kernel(SmallCArgs a) {
+template <int DT, int KS, int NB>
+__global__ __launch_bounds__(256, 2) void conv_small_c_kernel(SmallCArgs a) {
   using E = Elem<DT>;
   using raw = typename E::raw;
-  extern __shared__ __attribute__((aligned(16))) char smem[];   // small_c_lds_bytes
+  constexpr int CO = 16 * NB;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ unsigned long long exec_part[4];
-  __shared__ uint4 sink;   // target of the staging stores of out-of-range lanes
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nwn = a.Cout / 16, nwm = 4 / nwn;   // waves over column / row blocks
-  const int wn = wave % nwn, wm = wave / nwn;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, rl = lane & 15;
-  SPAROA_ARGS_UP_FRONT("s"(a.x), "s"(a.w), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.Ho), "s"(a.Cout),
-                       "s"(a.kh), "s"(a.sh), "s"(a.ph), "s"(a.w_elems), "s"(a.c_w),
-                       "s"(a.region_off), "s"(a.inv_rv), "s"(a.vec), "s"(a.mode),
+  SPAROA_ARGS_UP_FRONT("s"(a.x), "s"(a.w), "s"(a.H), "s"(a.W), "s"(a.C), "s"(a.Ho), "s"(a.kh),
+                       "s"(a.kw), "s"(a.sh), "s"(a.ph), "s"(a.pw), "s"(a.PWP), "s"(a.rw),
+                       "s"(a.groups), "s"(a.prows), "s"(a.patch_off), "s"(a.mode),
                        "s"(a.route.counts));
-  const int img = (int)(blockIdx.x / (unsigned)a.Ho), oh = (int)(blockIdx.x % (unsigned)a.Ho);
-  // the device route's counts are requested now and decided on once the
-  // weights and input rows are staged (nothing before needs the decision)
   const RouteCountsReq rq = route_counts_request(a.route);
-  // LDS: patch [kh][PWP][4] | region: weights [Cout*kh*kw*C], raw input rows
-  // [kh][W*C] while the operands are built, then the fp32 output tile
-  raw *patch = reinterpret_cast<raw *>(smem);
-  char *region = smem + a.region_off;
-  raw *wl = reinterpret_cast<raw *>(region);
-  raw *rawx = wl + a.w_elems;
-  float *ct = reinterpret_cast<float *>(region);
-  const raw *x = reinterpret_cast<const raw *>(a.x);
-  const raw *w = reinterpret_cast<const raw *>(a.w);
-  const int rowe = a.W * a.C;
-  const int ih0 = oh * a.sh - a.ph;
-  const int64_t img_base = (int64_t)img * a.H * rowe;
+  const int img = (int)(blockIdx.x / (unsigned)a.groups);
+  const int oh0 = (int)(blockIdx.x % (unsigned)a.groups) * a.rw;
+  const int ih0 = oh0 * a.sh - a.ph, rowe = a.W * a.C;
 
-  // ---- weights and the kh input rows -> LDS: loads unconditional (clamped
-  // addresses; rows outside the image are zeroed by the patch below) and
-  // independent, stores unconditional (no branch to sink the loads into)
-  if (a.vec) {
-    const int wv = a.w_elems / 8, rv = rowe / 8, nv = a.kh * rv;
-    for (int v0 = tid; v0 < wv + nv; v0 += 256 * 4) {
-      uint4 q[4];
+  // ---- weights -> LDS as K blocks [CO][WP] of 16 bytes, one block of
+  // padding per channel (conflict-free reads).  Consecutive lanes take
+  // consecutive blocks of a channel; a block's two taps are 4 C consecutive
+  // bytes, read with one 16-byte load from the dword below them (the last
+  // blocks: from the tensor's end, a multiple of 32 bytes) and moved into
+  // place.
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)a.w, (short)0, CO * a.kh * a.kw * a.C * 2, kBufDword3);
+  constexpr int WB = 4 * KS, WP = WB + 1;
+  constexpr int WIT = (WB * CO + 255) / 256;
+  const int tapb = 2 * a.C, wlast = CO * a.kh * a.kw * a.C * 2 - 16;
+  const uint64_t cmask = a.C == 4 ? ~0ull : (1ull << (8 * tapb)) - 1ull;
+  u32x4 wv[WIT];
+  int woff[WIT];   // byte offset of the block, negative past the kernel
+  bool whi[WIT];   // the block has a second tap
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int v = min(v0 + 256 * u, wv + nv - 1);
-        int r, cv;
-        divmod_small(max(v - wv, 0), rv, a.inv_rv, r, cv);
-        const int ih = min(max(ih0 + r, 0), a.H - 1);
-        const raw *src = v < wv ? w + (int64_t)v * 8
-                                : x + img_base + (int64_t)ih * rowe + (int64_t)cv * 8;
-        q[u] = *reinterpret_cast<const uint4 *>(src);
+  for (int u = 0; u < WIT; ++u) {
+    const int v = tid + 256 * u, co = v / WB, blk = v % WB;
+    int r, j;
+    divmod_small(blk, a.bpr, a.inv_bpr, r, j);
+    const bool in = co < CO && r < a.kh;
+    woff[u] = in ? ((co * a.kh + r) * a.kw + 2 * j) * tapb : -1;
+    whi[u] = 2 * j + 1 < a.kw;
+    wv[u] = __builtin_amdgcn_raw_buffer_load_b128(
+        wr, in ? min(woff[u] & ~3, wlast) : (int)0x80000000, 0, 0);
+  }
+  // ---- patch[row][q][c4] (q = input column + pw): zero outside the image
+  // and for channels >= C.  The buffer range starts at the first input row
+  // the image has (a work-group's rows stay within 32 bits whatever x holds).
+  const int ihb = max(ih0, 0), nin = max(min(ih0 + a.prows, a.H) - ihb, 0);
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(a.x + ((int64_t)img * a.H + ihb) * rowe * 2), (short)0, nin * rowe * 2, kBufDword3);
+  char *const patch = smem + a.patch_off;
+  const int npx = a.prows * a.PWP, xlast = nin * rowe * 2 - 8;
+  // PAIR: rows of whole dwords (W C even), at least one pair of them: a
+  // pixel's 2 C <= 8 bytes come with one 8-byte load from the dword below
+  // them; else element by element
+  auto stage_patch = [&](auto pair) __attribute__((always_inline)) {
+    constexpr bool PAIR = decltype(pair)::value;
+    constexpr int U = 4;
+    for (int p0 = tid; p0 < npx; p0 += 256 * U) {
+      uint64_t t[U];
+      int off[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        int pr, q;
+        divmod_small(p0 + 256 * u, a.PWP, a.inv_pwp, pr, q);
+        const int ih = ih0 + pr, iw = q - a.pw;
+        const bool in = ih >= ihb && ih < a.H && iw >= 0 && iw < a.W && pr < a.prows;
+        off[u] = in ? ((ih - ihb) * rowe + iw * a.C) * 2 : -1;
+        if constexpr (PAIR) {
+          typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+          const u32x2 d = __builtin_amdgcn_raw_buffer_load_b64(
+              xr, in ? min(off[u] & ~3, xlast) : (int)0x80000000, 0, 0);
+          t[u] = (uint64_t)d.x | (uint64_t)d.y << 32;
+        } else {
+          t[u] = 0;
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            t[u] |= (uint64_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(
+                        xr, in && c < a.C ? off[u] + 2 * c : (int)0x80000000, 0, 0)
+                    << (16 * c);
+        }
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int v = v0 + 256 * u;
-        *(v < wv + nv ? reinterpret_cast<uint4 *>(wl + (size_t)v * 8) : &sink) = q[u];
+      for (int u = 0; u < U; ++u) {
+        const int p = p0 + 256 * u;
+        if constexpr (PAIR) t[u] = t[u] >> (8 * max(off[u] - min(off[u] & ~3, xlast), 0)) & cmask;
+        if (p < npx) *reinterpret_cast<uint64_t *>(patch + (size_t)p * 8) = off[u] < 0 ? 0 : t[u];
       }
     }
-  } else {
-    const int ne = a.kh * rowe;
-    for (int e0 = tid; e0 < a.c_w + ne; e0 += 256 * 8) {
-      raw q[8];
+  };
+  auto stage = [&]() __attribute__((always_inline)) {
+    if (a.pair && xlast >= 0) stage_patch(std::true_type{});
+    else stage_patch(std::false_type{});
+  };
+  if (a.patch_off) stage();
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = min(e0 + 256 * u, a.c_w + ne - 1);
-        int r, ce;
-        divmod_small(max(e - a.c_w, 0), rowe, a.inv_rowe, r, ce);
-        const int ih = min(max(ih0 + r, 0), a.H - 1);
-        q[u] = e < a.c_w ? w[e] : x[img_base + (int64_t)ih * rowe + ce];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = e0 + 256 * u;
-        raw *dst = e < a.c_w ? wl + e : rawx + (e - a.c_w);
-        *(e < a.c_w + ne ? dst : reinterpret_cast<raw *>(&sink)) = q[u];
-      }
-    }
+  for (int u = 0; u < WIT; ++u) {
+    const int v = tid + 256 * u, s = woff[u] - min(woff[u] & ~3, wlast);   // bytes to drop, < 16
+    uint64_t lo = (uint64_t)wv[u][0] | (uint64_t)wv[u][1] << 32;
+    uint64_t hi = (uint64_t)wv[u][2] | (uint64_t)wv[u][3] << 32;
+    const bool far = s >= 8;
+    lo = far ? hi : lo;
+    hi = far ? 0ull : hi;
+    const int sb = 8 * (s & 7);
+    lo = lo >> sb | (sb ? hi << (64 - sb) : 0ull);
+    hi >>= sb;
+    const uint64_t second = a.C == 4 ? hi : lo >> (8 * tapb) | hi << (64 - 8 * tapb);
+    const bool in = woff[u] >= 0;
+    const uint64_t q[2] = {in ? lo & cmask : 0ull, in && whi[u] ? second & cmask : 0ull};
+    uint4 q4;
+    __builtin_memcpy(&q4, q, 16);
+    if (v < WB * CO) *reinterpret_cast<uint4 *>(smem + (v / WB * WP + v % WB) * 16) = q4;
   }
   __syncthreads();
+
+  // ---- weight operands: MFMA row 4 q + v of block b is channel
+  // 4 NB q + 4 b + v; lane group g holds K block 4 t + g.  The patch side
+  // keeps each block's offset and the all-ones / zero masks of its taps.
+  u32x4 wop[NB][KS];
+  int koff[KS];
+  uint32_t mlo[KS], mhi[KS];
+#pragma unroll
+  for (int t = 0; t < KS; ++t) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      wop[b][t] = *reinterpret_cast<const u32x4 *>(
+          smem + ((4 * NB * (rl >> 2) + 4 * b + (rl & 3)) * WP + 4 * t + g) * 16);
+    int r, j;
+    divmod_small(4 * t + g, a.bpr, a.inv_bpr, r, j);
+    const bool lo_ok = r < a.kh, hi_ok = lo_ok && 2 * j + 1 < a.kw;
+    mlo[t] = lo_ok ? 0xFFFFFFFFu : 0u;
+    mhi[t] = hi_ok ? 0xFFFFFFFFu : 0u;
+    koff[t] = (min(r, a.kh - 1) * a.PWP + 2 * j) * 8;
+  }
+  if (!a.patch_off) {   // the patch takes the weights' place
+    __syncthreads();
+    stage();
+    __syncthreads();
+  }
   bool skip = a.mode == 1;
   if (a.mode == 2) {
     skip = route_counts_skip(rq, a.route);
     if (a.route.path_out && blockIdx.x == 0 && tid == 0)
       *a.route.path_out = (skip ? 1u : 0u) | ((uint32_t)a.route.bw_bit << 1);
   }
+  constexpr int V = NB >= 2 ? NB / 2 : 1;   // output vectors of a lane: 8 channels (4: NB 1)
+  constexpr int CV = NB >= 2 ? 8 : 4;
+  const raw *bias = reinterpret_cast<const raw *>(a.bias);
+  float bf[4 * NB];
+#pragma unroll
+  for (int e = 0; e < 4 * NB; ++e) bf[e] = bias ? E::to_f32(bias[4 * NB * g + e]) : 0.f;
 
-  // ---- padded patch patch[r][q][c4] (q = input column + pw; zero outside
-  // the image and for channels >= C; one column past PW keeps every operand
-  // read in range): a thread owns columns, kernel rows inner
-  for (int q = tid; q < a.PWP; q += 256) {
-    const int iw = q - a.pw;
-    const bool col_in = iw >= 0 && iw < a.W;
-    const int iwc = min(max(iw, 0), a.W - 1) * a.C;
-    for (int r = 0; r < a.kh; ++r) {
-      const int ih = ih0 + r;
-      const bool in = col_in && ih >= 0 && ih < a.H;
-      const raw *src = rawx + r * rowe + iwc;
-      raw v[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {    // unconditional reads (clamped), then masked
-        const raw t = src[min(c, a.C - 1)];
-        v[c] = in && c < a.C ? t : (raw)0;
-      }
-      uint2 q2;
-      __builtin_memcpy(&q2, v, 8);
-      *reinterpret_cast<uint2 *>(patch + (size_t)(r * a.PWP + q) * 4) = q2;
-    }
-  }
-  // ---- B operands (registers): lane (column rl, group g) at k-step t holds
-  // K block b = 4t + g = (kernel row b / bpr, tap pair b % bpr); the A side
-  // keeps each block's patch offset and all-ones / zero masks of its taps
-  const int co = wn * 16 + rl;
-  int koff[KS];
-  uint32_t mlo[KS], mhi[KS];
-  u32x4 bop[KS];
-#pragma unroll
-  for (int t = 0; t < KS; ++t) {
-    int r, j;
-    divmod_small(4 * t + g, a.bpr, a.inv_bpr, r, j);
-    const int rc = min(r, a.kh - 1);
-    const bool lo_ok = r < a.kh, hi_ok = lo_ok && 2 * j + 1 < a.kw;
-    mlo[t] = lo_ok ? 0xFFFFFFFFu : 0u;
-    mhi[t] = hi_ok ? 0xFFFFFFFFu : 0u;
-    koff[t] = (rc * a.PWP + 2 * j) * 4;
-    const raw *wr = wl + ((co * a.kh + rc) * a.kw + 2 * j) * a.C;
-    const int s1 = min(2 * j + 1, a.kw - 1) - 2 * j;   // second tap (clamped)
-    raw v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int c = e & 3;
-      const raw wv = wr[(e >> 2) * s1 * a.C + min(c, a.C - 1)];
-      v[e] = (e < 4 ? lo_ok : hi_ok) && c < a.C ? wv : (raw)0;
-    }
-    __builtin_memcpy(&bop[t], v, 16);
-  }
-  __syncthreads();   // patch complete; weights and raw rows dead: the tile may reuse them
-
-  // ---- MFMAs, one 16-pixel row block at a time (this wave's rb = wm, wm +
-  // nwm, ...); each block's fp32 result goes straight to the tile
+  // ---- a wave's row (wave % rw) and share of its 16-pixel blocks
+  const int wrow = wave % a.rw, nparts = 4 / a.rw;
   const int RB = (a.Wo + 15) / 16;
-  const int CS = a.Cout + 4;
+  const int oh = oh0 + wrow;
   unsigned long long executed = 0;
-  for (int rb = wm; rb < RB; rb += nwm) {
-    const int ow = min(rb * 16 + rl, a.Wo - 1);  // rows past Wo read a valid pixel, unused
-    const int pix = ow * a.sw * 4;
+  uint32_t om_zeros = 0, om_nz = 0;
+  const int64_t row0 = ((int64_t)img * a.Ho + oh) * a.Wo;
+  // (one 16-pixel block; GEN: with the skip test and a residual)
+  auto block = [&](auto gen, int rb) __attribute__((always_inline)) {
+    constexpr bool GEN = decltype(gen)::value;
+    const int ow = rb * 16 + rl;
+    // (pixels past Wo read a valid one, unused)
+    const char *px = patch + (wrow * a.sh * a.PWP + min(ow, a.Wo - 1) * a.sw) * 8;
     u32x4 aops[KS];
 #pragma unroll
     for (int t = 0; t < KS; ++t) {   // all reads first
       // two 8-byte reads: a block starts on an 8-byte (not 16-byte) boundary
-      const uint2 lo = *reinterpret_cast<const uint2 *>(patch + koff[t] + pix);
-      const uint2 hi = *reinterpret_cast<const uint2 *>(patch + koff[t] + pix + 4);
+      const uint2 lo = *reinterpret_cast<const uint2 *>(px + koff[t]);
+      const uint2 hi = *reinterpret_cast<const uint2 *>(px + koff[t] + 8);
       aops[t] = u32x4{lo.x & mlo[t], lo.y & mlo[t], hi.x & mhi[t], hi.y & mhi[t]};
     }
-    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < KS; ++t) {
       const u32x4 aop = aops[t];
-      if (skip && __ballot((aop[0] | aop[1] | aop[2] | aop[3]) != 0u) == 0ull) continue;  // exact
-      executed += 1;
-      if constexpr (DT == SPAROA_BF16)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, aop),
-                                                      __builtin_bit_cast(bf16x8, bop[t]), acc,
-                                                      0, 0, 0);
-      else
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, aop),
-                                                     __builtin_bit_cast(f16x8, bop[t]), acc,
-                                                     0, 0, 0);
-    }
+      if (GEN && skip && __ballot((aop[0] | aop[1] | aop[2] | aop[3]) != 0u) == 0ull) continue;  // exact
+      if (GEN) executed += 1;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) ct[(rb * 16 + 4 * g + v) * CS + wn * 16 + rl] = acc[v];
+      for (int b = 0; b < NB; ++b) {
+        if constexpr (DT == SPAROA_BF16)
+          acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wop[b][t]),
+                                                           __builtin_bit_cast(bf16x8, aop), acc[b],
+                                                           0, 0, 0);
+        else
+          acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wop[b][t]),
+                                                          __builtin_bit_cast(f16x8, aop), acc[b],
+                                                          0, 0, 0);
+      }
+    }
+    // ---- epilogue: channels 4 NB g + [0, 4 NB) of pixel ow
+    const bool valid = ow < a.Wo;
+    const int64_t o = (row0 + ow) * CO + 4 * NB * g;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      raw t8[CV];
+      float f[CV];
+#pragma unroll
+      for (int e = 0; e < CV; ++e)
+        f[e] = acc[CV / 4 * v + (e >> 2)][e & 3] + bf[CV * v + e];
+      if (GEN && a.residual && valid) {
+        __builtin_memcpy(t8, reinterpret_cast<const raw *>(a.residual) + o + CV * v, 2 * CV);
+#pragma unroll
+        for (int e = 0; e < CV; ++e) f[e] += E::to_f32(t8[e]);
+      }
+      uint32_t w[CV / 2];
+#pragma unroll
+      for (int e = 0; e < CV / 2; ++e)
+        w[e] = E::pack2(apply_act(f[2 * e], a.act), apply_act(f[2 * e + 1], a.act));
+      if (valid) __builtin_memcpy(reinterpret_cast<raw *>(a.y) + o + CV * v, w, 2 * CV);
+      if (a.om_counts) {
+        uint32_t nz = nonzeros16<CV / 2>(w);
+        om_zeros += valid ? CV - nz : 0u;
+        if constexpr (NB == 1) {   // a block is two lanes' channels: counted by the even group
+          const uint32_t other = __shfl_xor(nz, 16, 64);   // (every lane takes part)
+          nz = (g & 1) ? 0u : nz + other;
+        }
+        om_nz += valid && nz ? 1u : 0u;
+      }
+    }
+  };
+  const int rb0 = oh < a.Ho ? wave / a.rw : RB;
+  if (skip || a.residual) {
+    for (int rb = rb0; rb < RB; rb += nparts) block(std::true_type{}, rb);
+  } else {
+    for (int rb = rb0; rb < RB; rb += nparts) block(std::false_type{}, rb);
   }
-  if (a.executed && skip && wn == 0 && lane == 0) exec_part[wm] = executed;
-  __syncthreads();
-
-  // ---- epilogue: 8 channels per thread, 16-byte stores
-  const int C8 = a.Cout / 8, lc8 = C8 == 8 ? 3 : (C8 == 4 ? 2 : 1);   // Cout in {16, 32, 64}
-  const raw *bias = reinterpret_cast<const raw *>(a.bias);
-  uint32_t om_zeros = 0, om_nz = 0;
-  const int64_t row0 = (int64_t)blockIdx.x * a.Wo;
-  for (int q = tid; q < a.Wo * C8; q += 256) {
-    const int ow = q >> lc8, c = (q & (C8 - 1)) * 8;
-    const int64_t orow = row0 + ow;
-    float o[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = ct[ow * CS + c + e];
-    raw t8[8];
-    if (bias) {
-      const uint4 q4 = *reinterpret_cast<const uint4 *>(bias + c);
-      __builtin_memcpy(t8, &q4, 16);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] += E::to_f32(t8[e]);
+  if (a.executed && skip) {
+    if (lane == 0) exec_part[wave] = executed;
+    __syncthreads();
+    if (tid == 0) {
+      const unsigned long long tot = exec_part[0] + exec_part[1] + exec_part[2] + exec_part[3];
+      if (tot) atomicAdd(a.executed, tot);
     }
-    if (a.residual) {
-      const uint4 q4 = *reinterpret_cast<const uint4 *>(
-          reinterpret_cast<const raw *>(a.residual) + orow * a.Cout + c);
-      __builtin_memcpy(t8, &q4, 16);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] += E::to_f32(t8[e]);
-    }
-    uint32_t any = 0;   // OR of the magnitudes
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      t8[e] = E::from_f32(apply_act(o[e], a.act));
-      // zero test in integer arithmetic (m - 1 wraps to bit 31 iff m == 0)
-      const uint32_t m = (uint32_t)t8[e] & E::mag_mask;
-      om_zeros += (m - 1u) >> 31;
-      any |= m;
-    }
-    om_nz += ((any - 1u) >> 31) ^ 1u;
-    uint4 q4;
-    __builtin_memcpy(&q4, t8, 16);
-    *reinterpret_cast<uint4 *>(reinterpret_cast<raw *>(a.y) + orow * a.Cout + c) = q4;
-  }
-  if (a.executed && skip && tid == 0) {
-    unsigned long long tot = 0;
-    for (int i = 0; i < nwm; ++i) tot += exec_part[i];
-    if (tot) atomicAdd(a.executed, tot);
   }
   if (a.om_counts) om_commit(om_zeros, om_nz, a.om_counts, a.om_words, blockIdx.x, gridDim.x);
 }
@@ -1514,25 +1539,6 @@ sparoa_status launch_split_reduce(const SplitReduceJob &job, hipStream_t stream)
 }
 
 namespace {
-// LDS of the direct small-channel kernel: raw input rows, weights (each
-// rounded up to whole 16-byte vectors) and the padded patch.
-int64_t small_c_raw_elems(const sparoa_conv_desc &d) { return cdiv(d.kh * d.w * d.c_in, 8) * 8; }
-int64_t small_c_w_elems(const sparoa_conv_desc &d) {
-  return cdiv(d.c_out * d.kh * d.kw * d.c_in, 8) * 8;
-}
-// LDS layout: patch [kh][PW + 1][4] | region: weights and raw rows, later the
-// fp32 output tile [16 * ceil(Wo / 16)][Cout + 4]
-int64_t small_c_region_off(const sparoa_conv_desc &d) {
-  const Shape s = shape_of(d);
-  return cdiv(d.kh * (d.sw * (s.wo - 1) + d.kw + 1) * 8, 16) * 16;
-}
-int64_t small_c_lds_bytes(const sparoa_conv_desc &d) {
-  const Shape s = shape_of(d);
-  const int64_t staged = 2 * (small_c_raw_elems(d) + small_c_w_elems(d));
-  const int64_t tile = 16 * cdiv(s.wo, 16) * (d.c_out + 4) * 4;
-  return small_c_region_off(d) + (staged > tile ? staged : tile);
-}
-
 // Shapes the direct small-channel kernel serves (image stems).
 bool small_c_eligible(const sparoa_conv_desc &d) {
   if (d.dtype == SPAROA_F32 || d.groups != 1 || d.dh != 1 || d.dw != 1) return false;
@@ -1541,7 +1547,23 @@ bool small_c_eligible(const sparoa_conv_desc &d) {
   const Shape s = shape_of(d);
   if (s.wo > 16 * kScMaxRB || d.n * s.ho >= ((int64_t)1 << 31)) return false;
   if (cdiv(d.kh * ((d.kw + 1) / 2), 4) > kScMaxKSteps) return false;
-  return small_c_lds_bytes(d) <= kScPatchBytes;
+  // one output row's patch [kh][PW + 1][4] beside its input rows and weights,
+  // or beside its fp32 outputs, within kScPatchBytes
+  const int64_t patch = cdiv(d.kh * (d.sw * (s.wo - 1) + d.kw + 1) * 8, 16) * 16;
+  const int64_t staged = 2 * (cdiv(d.kh * d.w * d.c_in, 8) * 8 +
+                              cdiv(d.c_out * d.kh * d.kw * d.c_in, 8) * 8);
+  const int64_t tile = 16 * cdiv(s.wo, 16) * (d.c_out + 4) * 4;
+  return patch + (staged > tile ? staged : tile) <= kScPatchBytes;
+}
+
+template <int DT, int KS>
+void launch_small_c_kernel(int nb, dim3 grid, unsigned lds, hipStream_t st, const SmallCArgs &a) {
+  if (nb == 4)
+    hipLaunchKernelGGL((conv_small_c_kernel<DT, KS, 4>), grid, dim3(256), lds, st, a);
+  else if (nb == 2)
+    hipLaunchKernelGGL((conv_small_c_kernel<DT, KS, 2>), grid, dim3(256), lds, st, a);
+  else
+    hipLaunchKernelGGL((conv_small_c_kernel<DT, KS, 1>), grid, dim3(256), lds, st, a);
 }
 
 sparoa_status launch_small_c(const sparoa_conv_desc &d, const void *x, const void *w,
@@ -1558,37 +1580,44 @@ sparoa_status launch_small_c(const sparoa_conv_desc &d, const void *x, const voi
   a.residual = static_cast<const char *>(residual);
   a.y = static_cast<char *>(y);
   a.executed = reinterpret_cast<unsigned long long *>(skip ? executed : nullptr);
-  a.N = (int)d.n; a.H = (int)d.h; a.W = (int)d.w; a.C = (int)d.c_in;
+  a.H = (int)d.h; a.W = (int)d.w; a.C = (int)d.c_in;
   a.Ho = (int)s.ho; a.Wo = (int)s.wo; a.Cout = (int)d.c_out;
   a.kh = (int)d.kh; a.kw = (int)d.kw; a.sh = (int)d.sh; a.sw = (int)d.sw;
   a.ph = (int)d.ph; a.pw = (int)d.pw;
-  a.PW = (int)(d.sw * (s.wo - 1) + d.kw);
-  a.PWP = a.PW + 1;
+  a.PWP = (int)(d.sw * (s.wo - 1) + d.kw + 1);   // one column past the last tap
+  a.pair = d.w * d.c_in % 2 == 0;
   a.bpr = (int)((d.kw + 1) / 2);
-  a.ksteps = (int)cdiv(d.kh * a.bpr, 4);
-  a.raw_elems = (int)small_c_raw_elems(d);
-  a.w_elems = (int)small_c_w_elems(d);
-  a.c_w = (int)(d.c_out * d.kh * d.kw * d.c_in);
-  // whole vectors: each input row and the weight tensor a multiple of 8 elements
-  a.vec = (d.w * d.c_in) % 8 == 0 && (d.c_out * d.kh * d.kw * d.c_in) % 8 == 0;
+  const int ksteps = (int)cdiv(d.kh * a.bpr, 4);
   a.inv_bpr = 1.0f / (float)a.bpr;
-  a.inv_rv = a.vec ? 1.0f / (float)(d.w * d.c_in / 8) : 0.0f;
-  a.inv_rowe = 1.0f / (float)(d.w * d.c_in);
-  a.region_off = (int)small_c_region_off(d);
+  a.inv_pwp = 1.0f / (float)a.PWP;
+  // Output rows per work-group: weights are laid out once per work-group and
+  // neighbouring rows share input rows, so 4 where that still leaves 384
+  // work-groups, else 2, else 1 (ResNet-50's stem at N = 8, 896 rows: 2 rows
+  // 12.5 us, 1 row 17.9 us; at N = 1, 112 rows, latency).
+  const int64_t rows = d.n * s.ho;
+  const int wbytes = (4 * ksteps + 1) * (int)d.c_out * 16;
+  auto patch_bytes = [&](int64_t rw) { return ((rw - 1) * d.sh + d.kh) * a.PWP * 8; };
+  a.rw = rows >= 4 * 384 ? 4 : (rows >= 2 * 384 ? 2 : 1);
+  while (a.rw > 1 && wbytes + patch_bytes(a.rw) > kScLdsBytes) a.rw /= 2;
+  a.prows = (a.rw - 1) * a.sh + a.kh;
+  const int64_t both = wbytes + patch_bytes(a.rw);
+  a.patch_off = both <= kScLdsBytes ? wbytes : 0;
+  const unsigned lds = (unsigned)(a.patch_off ? both
+                                              : (patch_bytes(a.rw) > wbytes ? patch_bytes(a.rw)
+                                                                            : wbytes));
+  a.groups = (int)cdiv(s.ho, a.rw);
   a.act = act;
   a.mode = route && route->counts ? 2 : (skip ? 1 : 0);
   a.route = route ? *route : DeviceRoute{nullptr, 0.0, 0, 0, nullptr};
   a.om_counts = om ? om->counts : nullptr;
   a.om_words = om ? om->words : nullptr;
-  const dim3 grid((unsigned)(d.n * s.ho));
-  const unsigned lds = (unsigned)small_c_lds_bytes(d);   // <= kScPatchBytes (eligibility)
-  switch (a.ksteps) {
+  const dim3 grid((unsigned)(d.n * a.groups));
+  const int nb = (int)d.c_out / 16;
+  switch (ksteps) {
 #define SPAROA_SC(K)                                                                         \
-  case K:                                                                                  \
-    if (d.dtype == SPAROA_BF16)                                                            \
-      hipLaunchKernelGGL((conv_small_c_kernel<SPAROA_BF16, K>), grid, dim3(256), lds, stream, a); \
-    else                                                                                   \
-      hipLaunchKernelGGL((conv_small_c_kernel<SPAROA_F16, K>), grid, dim3(256), lds, stream, a);  \
+  case K:                                                                                    \
+    if (d.dtype == SPAROA_BF16) launch_small_c_kernel<SPAROA_BF16, K>(nb, grid, lds, stream, a); \
+    else launch_small_c_kernel<SPAROA_F16, K>(nb, grid, lds, stream, a);                     \
     break;
     SPAROA_SC(1) SPAROA_SC(2) SPAROA_SC(3) SPAROA_SC(4)
     SPAROA_SC(5) SPAROA_SC(6) SPAROA_SC(7) SPAROA_SC(8)
