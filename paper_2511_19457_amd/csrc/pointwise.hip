@@ -14,11 +14,17 @@
 // comes from LDS, the B operand (32 k x 16 pixels) straight from global
 // memory -- lane (pixel p, group g) loads the 16 bytes of channels
 // 8g..8g+7 of its pixel, so a wave's load is 16 pixel rows of 64 contiguous
-// bytes -- and each lane ends with 4 consecutive output channels of one
-// pixel; lanes g and g ^ 1 then swap halves so each finishes 8 consecutive
-// channels of its pixel with 16-byte residual loads and stores.  K (= C_in)
-// is at most 256: all of a tile's activation loads are issued before its
-// first MFMA, and the next tile's while the current one computes.
+// bytes.  The weight rows lie in LDS in an order that leaves each lane 8
+// consecutive output channels of its pixel per block pair: four lanes store
+// 64 consecutive bytes, with no exchange between lanes.  K (= C_in) is at
+// most 256: all of a tile's activation loads are issued before its first
+// MFMA, the next tile's while the current one computes, and the tile's
+// residual vectors (a separate instantiation) before its MFMAs: loads issued
+// behind stores wait for them here.  Bound by HBM and by the loads a CU keeps
+// in flight: [32,56,56,64] -> 256 bf16 with residual, counts and bitmap 46 ->
+// 34 us (alternating buffers, 3.4 TB/s) against the form that swapped halves
+// between lanes and read each residual vector behind the stores of the one
+// before; the next tile's residual prefetched too, 36 us.
 //
 // Zero skipping (Section 2.1): in the skip form an MFMA group whose B
 // operand is zero in all 64 lanes -- a 16-pixel x 32-channel block of zero
@@ -76,8 +82,14 @@ __device__ __forceinline__ void divmod_f(int n, int d, float inv_d, int &q, int 
   r = lo ? r0 + d : (hi ? r0 - d : r0);
 }
 
-template <int DT, int NB, int R, int KS>
-__global__ __launch_bounds__(kPwThreads) void pointwise_kernel(PwArgs a) {
+// Waves per SIMD asked of the compiler: three where the accumulators and the
+// two tiles of activations leave room (144 -> 24 at 56 x 56, N = 32 13.2 ->
+// 11.9 us), else two (64 -> 256 with residual: two 34 us, three 37 us, four
+// spill; without a bound it took 284 registers, one wave, 51 us).
+constexpr int pw_waves(int nb, int r, int ks) { return r * nb * 4 + 8 * r * ks <= 72 ? 3 : 2; }
+
+template <int DT, int NB, int R, int KS, bool RES>
+__global__ __launch_bounds__(kPwThreads, pw_waves(NB, R, KS)) void pointwise_kernel(PwArgs a) {
   using E = Elem<DT>;
   using raw = typename E::raw;
   constexpr int P = 64 * R;              // output pixels per tile
@@ -112,8 +124,12 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_kernel(PwArgs a) {
     for (int u = 0; u < 8; ++u) {
       const int v = v0 + kPwThreads * u;
       const int row = v / vpr, kv = v - row * vpr;
-      const int oc = c0 + row, k = kv * 8;
-      ok[u] = v < nv && oc < a.Cout && row < a.bn && k < a.K;
+      // LDS row 16 j + 4 q + t of block j holds channel 32 (j / 2) + 8 q +
+      // 4 (j % 2) + t of the slice (one block alone: in order)
+      const int j = row >> 4, q4 = (row >> 2) & 3, t4 = row & 3;
+      const int ch = NB == 1 ? row : 32 * (j >> 1) + 8 * q4 + 4 * (j & 1) + t4;
+      const int oc = c0 + ch, k = kv * 8;
+      ok[u] = v < nv && oc < a.Cout && ch < a.bn && k < a.K;
       q[u] = *reinterpret_cast<const uint4 *>(w + (ok[u] ? (int64_t)oc * a.K + k : 0));
     }
 #pragma unroll
@@ -167,53 +183,43 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_kernel(PwArgs a) {
     }
   };
 
-  // Finishes 8 consecutive output channels c0 + oc8 .. + 7 of pixel m (one
-  // bitmap block): bias, residual, activation, one 16-byte store, and the
-  // block's zero count and nonzero bit.
-  auto finish8 = [&](int m, int p0, int oc8, const float (&v)[8]) __attribute__((always_inline)) {
-    if (m >= a.M || oc8 >= a.bn || c0 + oc8 >= a.Cout) return;
-    const int oc = c0 + oc8;
-    float o[8];
+  // This lane's output vectors of a pixel: 8 channels at c0 + 32 jp + 8 g per
+  // block pair jp (one block alone: 4 channels at c0 + 4 g).
+  constexpr int NP = NB == 1 ? 1 : NB / 2, CV = NB == 1 ? 4 : 8;
+  static_assert(NB == 1 || NB % 2 == 0, "block pairs");
+  typedef uint32_t vec_t __attribute__((ext_vector_type(CV / 2)));
+  auto ch_of = [&](int jp) __attribute__((always_inline)) { return 32 * jp + CV * g; };
+  auto load_res = [&](int tile, vec_t (&rv)[R][NP]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = v[e];
-    raw t[8];
-    if (bias) {
-      const uint4 q = *reinterpret_cast<const uint4 *>(bias + oc);
-      __builtin_memcpy(t, &q, 16);
+    for (int r = 0; r < R; ++r) {
+      const int m = tile * P + (wave * R + r) * 16 + rl;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] += E::to_f32(t[e]);
-    }
-    if (res) {
-      const uint4 q = *reinterpret_cast<const uint4 *>(res + (int64_t)m * a.Cout + oc);
-      __builtin_memcpy(t, &q, 16);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] += E::to_f32(t[e]);
-    }
-    uint32_t nz = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      t[e] = E::from_f32(apply_act(o[e], a.act));
-      const bool z = (t[e] & 0x7FFFu) == 0u;
-      om_zeros += (om && z) ? 1u : 0u;
-      nz |= z ? 0u : 1u;
-    }
-    uint4 q;
-    __builtin_memcpy(&q, t, 16);
-    *reinterpret_cast<uint4 *>(y + (int64_t)m * a.Cout + oc) = q;
-    if (om && nz) {
-      const int bit = (m - p0) * C8 + oc / 8;
-      atomicOr(&ombits[bit >> 5], 1u << (bit & 31));
-      om_nz += 1;
+      for (int jp = 0; jp < NP; ++jp) {
+        const int ch = ch_of(jp);
+        rv[r][jp] = vec_t{};
+        if (m < a.M && ch < a.bn && c0 + ch < a.Cout)
+          rv[r][jp] = *reinterpret_cast<const vec_t *>(res + (int64_t)m * a.Cout + c0 + ch);
+      }
     }
   };
+  // bitmap: whole bytes from ballots where a pixel's blocks are whole bytes,
+  // else bits gathered in LDS
+  const bool om_bytes = NB % 4 == 0 && a.om_mask && C8 % 8 == 0;
+  const bool om_lds = a.om_mask && !om_bytes;
 
   u32x4 cur[R][KS], nxt[R][KS];
+  vec_t rv[RES ? R : 1][RES ? NP : 1];
   int tile = wg_in_slice;
-  if (tile < a.tiles) load_tile(tile, cur);
+  if (tile < a.tiles) {
+    load_tile(tile, cur);
+  }
   for (; tile < a.tiles; tile += wgs_per_slice) {
     const int p0 = tile * P;
     const int next = tile + wgs_per_slice;
-    if (next < a.tiles) load_tile(next, nxt);   // the next tile's loads fly during this one
+    if (next < a.tiles) {   // the next tile's loads fly during this one
+      load_tile(next, nxt);
+    }
+    if constexpr (RES) load_res(tile, rv);
     f32x4 acc[R][NB];
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -253,45 +259,75 @@ __global__ __launch_bounds__(kPwThreads) void pointwise_kernel(PwArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
 
-    // ---- epilogue.  Lane (pixel rl, group g) holds channels 16 j + 4 g .. + 3
-    // of block j.  For a block pair (j, j + 1) lanes g and g ^ 1 swap halves so
-    // each lane holds 8 consecutive channels of its pixel: even g channels
-    // 32 jp + 8 (g / 2) .., odd g channels 32 jp + 16 + 8 (g / 2) ..
-    if (om) {
+    // ---- epilogue: bias, residual, activation, one store per vector, and
+    // each 8-channel block's zero count and nonzero bit
+    if (om_lds) {
       for (int i = tid; i < P * C8 / 32; i += kPwThreads) ombits[i] = 0u;
       __syncthreads();
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int m = p0 + (wave * R + r) * 16 + rl;
+      uint64_t below = 0;   // the ballot of the even pair of a 64-channel group
 #pragma unroll
-      for (int jp = 0; jp + 1 < NB; jp += 2) {
-        const bool odd = (g & 1) != 0;
-        float v[8];
+      for (int jp = 0; jp < NP; ++jp) {
+        const int ch = ch_of(jp), oc = c0 + ch;
+        const bool valid = m < a.M && ch < a.bn && oc < a.Cout;
+        float o[CV];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float send = odd ? acc[r][jp][e] : acc[r][jp + 1][e];
-          const float recv = __shfl_xor(send, 16, 64);
-          v[e] = odd ? recv : acc[r][jp][e];
-          v[4 + e] = odd ? acc[r][jp + 1][e] : recv;
+        for (int e = 0; e < CV; ++e) o[e] = acc[r][NB == 1 ? 0 : 2 * jp + (e >> 2)][e & 3];
+        raw t[CV];
+        if (bias && valid) {
+          __builtin_memcpy(t, bias + oc, 2 * CV);
+#pragma unroll
+          for (int e = 0; e < CV; ++e) o[e] += E::to_f32(t[e]);
         }
-        finish8(m, p0, 16 * jp + (odd ? 16 : 0) + 8 * (g >> 1), v);
-      }
-      if constexpr (NB % 2 == 1) {
-        // the last block alone: lanes g and g ^ 1 hold channels 8 (g / 2) ..;
-        // the even lane takes the odd lane's four
-        constexpr int j = NB - 1;
-        float v[8];
+        if constexpr (RES) {
+          __builtin_memcpy(t, &rv[r][jp], 2 * CV);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float recv = __shfl_xor(acc[r][j][e], 16, 64);
-          v[e] = acc[r][j][e];
-          v[4 + e] = recv;
+          for (int e = 0; e < CV; ++e) o[e] += E::to_f32(t[e]);
         }
-        if ((g & 1) == 0) finish8(m, p0, 16 * j + 8 * (g >> 1), v);
+        uint32_t w[CV / 2];
+#pragma unroll
+        for (int e = 0; e < CV / 2; ++e)
+          w[e] = E::pack2(apply_act(o[2 * e], a.act), apply_act(o[2 * e + 1], a.act));
+        if (valid) __builtin_memcpy(y + (int64_t)m * a.Cout + oc, w, 2 * CV);
+        if (om) {
+          uint32_t nz = nonzeros16<CV / 2>(w);
+          om_zeros += valid ? CV - nz : 0u;
+          if constexpr (NB == 1) {   // a block is two lanes' channels: counted by the even group
+            const uint32_t other = __shfl_xor(nz, 16, 64);
+            nz = (g & 1) ? 0u : nz + other;
+          }
+          const bool nzb = valid && nz != 0u;
+          om_nz += nzb ? 1u : 0u;
+          if (om_bytes) {
+            // block 4 (jp % 2) + g of the group's byte
+            const uint64_t bal = __ballot(nzb);
+            if (jp % 2 == 0) {
+              below = bal;
+            } else if (g == 0 && m < a.M && c0 + 32 * (jp - 1) < a.Cout && 32 * (jp - 1) < a.bn) {
+              uint32_t v = 0;
+#pragma unroll
+              for (int q = 0; q < 4; ++q)
+                v |= ((uint32_t)(below >> (rl + 16 * q)) & 1u) << q |
+                     ((uint32_t)(bal >> (rl + 16 * q)) & 1u) << (4 + q);
+              reinterpret_cast<uint8_t *>(a.om_mask)[(int64_t)m * (C8 / 8) + oc / 64] = (uint8_t)v;
+            }
+          }
+          if (om_lds && nzb) {
+            const int bit = (m - p0) * C8 + oc / 8;
+            atomicOr(&ombits[bit >> 5], 1u << (bit & 31));
+          }
+        }
       }
     }
-    if (om) {
+    if (om_bytes && p0 + P >= a.M) {   // the last word's bytes past the last block
+      const int64_t first = (int64_t)a.M * (C8 / 8), end = 4 * a.om_mask_words;
+      if (first + tid < end && tid < 4)
+        reinterpret_cast<uint8_t *>(a.om_mask)[first + tid] = 0;
+    }
+    if (om_lds) {
       __syncthreads();
       const int64_t w0 = (int64_t)p0 * C8 / 32;
       for (int i = tid; i < P * C8 / 32; i += kPwThreads)
@@ -374,33 +410,34 @@ bool pw_choose(const sparoa_conv_desc &d, PwChoice *c) {
 }
 
 template <int DT, int NB, int R, int KS>
-const void *pw_fn() {
-  return reinterpret_cast<const void *>(&pointwise_kernel<DT, NB, R, KS>);
+const void *pw_fn(bool res) {
+  return res ? reinterpret_cast<const void *>(&pointwise_kernel<DT, NB, R, KS, true>)
+             : reinterpret_cast<const void *>(&pointwise_kernel<DT, NB, R, KS, false>);
 }
 
 // The (NB, KS) pairs pw_choose can select, R fixed by them.
 template <int DT, int NB>
-const void *pw_kernel_nb(int r, int ks) {
+const void *pw_kernel_nb(int r, int ks, bool res) {
   constexpr int R1 = NB <= 4 ? 4 : (NB <= 8 ? 2 : 1);      // KS = 1, 2
   constexpr int R4 = NB <= 8 ? 2 : 1;                      // KS = 4
-  if (ks == 1 && r == R1) return pw_fn<DT, NB, R1, 1>();
-  if (ks == 2 && r == R1) return pw_fn<DT, NB, R1, 2>();
-  if (ks == 4 && r == R4) return pw_fn<DT, NB, R4, 4>();
+  if (ks == 1 && r == R1) return pw_fn<DT, NB, R1, 1>(res);
+  if (ks == 2 && r == R1) return pw_fn<DT, NB, R1, 2>(res);
+  if (ks == 4 && r == R4) return pw_fn<DT, NB, R4, 4>(res);
   if constexpr (NB <= 4 || NB >= 12)
-    if (ks == 8 && r == 1) return pw_fn<DT, NB, 1, 8>();
+    if (ks == 8 && r == 1) return pw_fn<DT, NB, 1, 8>(res);
   return nullptr;
 }
 
 template <int DT>
-const void *pw_kernel(int nb, int r, int ks) {
+const void *pw_kernel(int nb, int r, int ks, bool res) {
   switch (nb) {
-    case 1: return pw_kernel_nb<DT, 1>(r, ks);
-    case 2: return pw_kernel_nb<DT, 2>(r, ks);
-    case 4: return pw_kernel_nb<DT, 4>(r, ks);
-    case 6: return pw_kernel_nb<DT, 6>(r, ks);
-    case 8: return pw_kernel_nb<DT, 8>(r, ks);
-    case 12: return pw_kernel_nb<DT, 12>(r, ks);
-    case 16: return pw_kernel_nb<DT, 16>(r, ks);
+    case 1: return pw_kernel_nb<DT, 1>(r, ks, res);
+    case 2: return pw_kernel_nb<DT, 2>(r, ks, res);
+    case 4: return pw_kernel_nb<DT, 4>(r, ks, res);
+    case 6: return pw_kernel_nb<DT, 6>(r, ks, res);
+    case 8: return pw_kernel_nb<DT, 8>(r, ks, res);
+    case 12: return pw_kernel_nb<DT, 12>(r, ks, res);
+    case 16: return pw_kernel_nb<DT, 16>(r, ks, res);
   }
   return nullptr;
 }
@@ -457,8 +494,9 @@ sparoa_status launch_pointwise(const sparoa_conv_desc &d, const void *x, const v
   a.om_words = om ? om->words : nullptr;
   a.om_mask_words = a.om_mask ? (a.M * (int64_t)(d.c_out / 8) + 31) / 32 : 0;   // null: counts only
   const unsigned lds = (unsigned)(c.nb * 16 * c.row_bytes);
-  const void *fn = d.dtype == SPAROA_BF16 ? pw_kernel<SPAROA_BF16>(c.nb, c.r, c.ksi)
-                                          : pw_kernel<SPAROA_F16>(c.nb, c.r, c.ksi);
+  const bool res = residual != nullptr;
+  const void *fn = d.dtype == SPAROA_BF16 ? pw_kernel<SPAROA_BF16>(c.nb, c.r, c.ksi, res)
+                                          : pw_kernel<SPAROA_F16>(c.nb, c.r, c.ksi, res);
   if (!fn) return fail(SPAROA_ERR_UNSUPPORTED, "pointwise: tile configuration");
   // persistent work-groups, as many as are resident at once, each bound to
   // one slice: every work-group stages its weights once for many tiles
