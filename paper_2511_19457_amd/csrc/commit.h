@@ -14,6 +14,22 @@ namespace sparoa {
 constexpr int kOmGroups = 8;
 constexpr int kOmDirectMax = 64;   // grids up to this many work-groups commit directly
 static_assert(2 * kOmGroups * 128 == SPAROA_COMMIT_WORDS_BYTES, "commit word layout");
+// Packed commit: both counts and the ticket in one word, 16 groups of one
+// word each (the same lines): ticket from bit 52, zeros from bit 24, nonzero
+// blocks below.  One returning atomic per work-group instead of two, and half
+// the members on a word.
+constexpr int kOmPackedGroups = 2 * kOmGroups;
+
+// The words argument of om_commit for an output of numel elements measured by
+// nwg work-groups: bit 0 marks the packed commit, taken where no field can
+// overflow (a group's zeros < 2^28, its blocks of 8 < 2^24, its members <
+// 2^12).
+inline unsigned long long *om_words_for(unsigned long long *words, int64_t numel, int64_t nwg) {
+  const bool packed = numel < ((int64_t)1 << 27) && nwg / kOmPackedGroups < 4095;
+  return words && packed ? reinterpret_cast<unsigned long long *>(
+                               reinterpret_cast<uintptr_t>(words) | 1u)
+                         : words;
+}
 
 // Adds a work-group's zero count and nonzero-block count into counts
 // (zero_blocks starts at nb).  Same-address atomics serialise device-wide
@@ -22,7 +38,8 @@ static_assert(2 * kOmGroups * 128 == SPAROA_COMMIT_WORDS_BYTES, "commit word lay
 // a member of group b % kOmGroups: each member adds (1 << 40) + its count to
 // its group's word with one returning atomic, and the member whose add
 // completes the group adds the group's total to counts and clears the word
-// for the next call.  Without `words`, or for a grid of at most
+// for the next call (om_words_for: both counts in one word where they fit).
+// Without `words`, or for a grid of at most
 // kOmDirectMax work-groups: one atomic per counter per work-group (the words
 // are left untouched).
 __device__ __forceinline__ void om_commit(uint32_t zeros, uint32_t nz, sparoa_counts *counts,
@@ -52,6 +69,26 @@ __device__ __forceinline__ void om_commit(uint32_t zeros, uint32_t nz, sparoa_co
     if (!words || nwg <= kOmDirectMax) {
       if (z) atomicAdd((unsigned long long *)&counts->zeros, z);
       if (n) atomicAdd((unsigned long long *)&counts->zero_blocks, 0ull - n);
+      return;
+    }
+    if (reinterpret_cast<uintptr_t>(words) & 1u) {
+      constexpr int kT = 52, kZ = 24;
+      const int64_t g = b % kOmPackedGroups;
+      const unsigned long long members = (unsigned long long)(
+          nwg / kOmPackedGroups + (g < nwg % kOmPackedGroups ? 1 : 0));
+      unsigned long long *w = reinterpret_cast<unsigned long long *>(
+                                  reinterpret_cast<uintptr_t>(words) & ~(uintptr_t)1) +
+                              g * 16;
+      const unsigned long long mine = (1ull << kT) + (z << kZ) + n;
+      const unsigned long long old = atomicAdd(w, mine);
+      if ((old >> kT) == members - 1) {
+        const unsigned long long t = old + mine;
+        const unsigned long long tz = (t >> kZ) & ((1ull << (kT - kZ)) - 1);
+        const unsigned long long tn = t & ((1ull << kZ) - 1);
+        if (tz) atomicAdd((unsigned long long *)&counts->zeros, tz);
+        if (tn) atomicAdd((unsigned long long *)&counts->zero_blocks, 0ull - tn);
+        atomicExch(w, 0ull);
+      }
       return;
     }
     constexpr unsigned long long kTicket = 1ull << 40;  // sums < 2^40, members < 2^24

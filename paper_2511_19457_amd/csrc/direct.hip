@@ -535,11 +535,12 @@ int64_t dw_grid(int64_t items, int64_t cv, int64_t cap) {
 }
 
 template <int DT, int S, int R, int RH>
-sparoa_status launch_dw3(const DwArgs &a, hipStream_t st, const FastDiv &fcv, int64_t cv) {
+sparoa_status launch_dw3(DwArgs a, hipStream_t st, const FastDiv &fcv, int64_t cv) {
   const int64_t runs = a.Wo / R;
   const int64_t items = a.N * (a.Ho / RH) * runs * cv;
   const FastDiv fruns = make_fastdiv((uint32_t)runs), fho = make_fastdiv((uint32_t)(a.Ho / RH));
   const int64_t nb = dw_grid(items, cv, 4096);
+  a.om_words = om_words_for(a.om_words, a.N * a.Ho * a.Wo * cv * 8, nb);
   if (a.om_counts)   // counts only (no bitmap)
     hipLaunchKernelGGL((dw3x3_kernel<DT, S, R, RH, true>), dim3((unsigned)nb), dim3(kThreads), 0,
                        st, a, fcv, fruns, fho);
@@ -551,10 +552,10 @@ sparoa_status launch_dw3(const DwArgs &a, hipStream_t st, const FastDiv &fcv, in
 }
 
 template <int DT, int S>
-sparoa_status launch_dw3_measured(const DwArgs &a, hipStream_t st, const FastDiv &fcv,
-                                  int64_t cv) {
+sparoa_status launch_dw3_measured(DwArgs a, hipStream_t st, const FastDiv &fcv, int64_t cv) {
   const int64_t items = a.N * a.Ho * a.Wo * cv;
   const int64_t nb = dw_grid(items, cv, 4096);
+  a.om_words = om_words_for(a.om_words, items * 8, nb);
   const int64_t om_words = cdiv(items, 32);
   hipLaunchKernelGGL((dw3x3_measured_kernel<DT, S>), dim3((unsigned)nb), dim3(kThreads), 0, st,
                      a, fcv, make_fastdiv((uint32_t)a.Wo), make_fastdiv((uint32_t)a.Ho),

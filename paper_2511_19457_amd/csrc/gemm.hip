@@ -1513,7 +1513,7 @@ sparoa_status launch_split_reduce_group(const SplitReduceJob *jobs, int n, hipSt
     g.y[j] = static_cast<char *>(r.y);
     g.om_counts[j] = r.om_counts;
     g.om_mask[j] = r.om_mask;
-    g.om_words[j] = r.om_words;
+    g.om_words[j] = om_words_for(r.om_words, r.M * r.N, blocks);
     if (r.om_counts && (elem_size(r.dt) != 2 || r.N % 8 != 0))
       return fail(SPAROA_ERR_UNSUPPORTED, "split reduce: output measurement needs 16-bit, N % 8 == 0");
     wg += blocks;
@@ -1610,8 +1610,8 @@ sparoa_status launch_small_c(const sparoa_conv_desc &d, const void *x, const voi
   a.mode = route && route->counts ? 2 : (skip ? 1 : 0);
   a.route = route ? *route : DeviceRoute{nullptr, 0.0, 0, 0, nullptr};
   a.om_counts = om ? om->counts : nullptr;
-  a.om_words = om ? om->words : nullptr;
   const dim3 grid((unsigned)(d.n * a.groups));
+  a.om_words = om ? om_words_for(om->words, s.M * s.N, grid.x) : nullptr;
   const int nb = (int)d.c_out / 16;
   switch (ksteps) {
 #define SPAROA_SC(K)                                                                         \
@@ -1884,6 +1884,7 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
     if (ntmn * gz >= (int64_t)1 << 24)
       return fail(SPAROA_ERR_UNSUPPORTED, "GEMM: 2^24 tiles or more");
     grid = dim3((unsigned)(ntmn * gz));
+    a.om_words = om_words_for(a.om_words, s.M * s.N, ntmn);
     const int64_t gw = cdiv(ntn, ig_column_groups(ntn, a.x_bytes, a.w_bytes));
     const int64_t gt = ntmn / ntn * gw, lastw = ntn - (cdiv(ntn, gw) - 1) * gw;
     a.ntn32 = (int)ntn;

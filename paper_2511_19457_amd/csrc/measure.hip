@@ -627,7 +627,8 @@ sparoa_status launch_measure_counts8(const void *x, sparoa_dtype dt, int64_t row
   }
   int64_t gx = cdiv(items, (int64_t)kLanebitThreads);
   if (gx > 256) gx = 256;
-  unsigned long long *cw = reinterpret_cast<unsigned long long *>(commit_words);
+  unsigned long long *cw =
+      om_words_for(reinterpret_cast<unsigned long long *>(commit_words), rows * cols, gx);
   if (h)
     hipLaunchKernelGGL((measure_lanebit<2, 8>), dim3((unsigned)gx), dim3(kLanebitThreads), 0,
                        stream, xc, items, (int64_t)0, (uint32_t *)nullptr, counts, cw);
@@ -704,34 +705,37 @@ sparoa_status launch_measure(const void *x, sparoa_dtype dt, int64_t rows, int64
   if (lanebit) {
     const int64_t items = rows * (cols / lv);
     // one work-group per CU where the tensor fills them (one item per lane
-    // at the least); with commit words a work-group's commit costs two
-    // returning atomics spread over 16 addresses, so a small tensor is spread
-    // over as many compute units as it has 1024-item slots
+    // at the least); with commit words a work-group's commit costs one
+    // returning atomic spread over 16 addresses (two above 2^27 elements), so
+    // a small tensor is spread over as many compute units as it has 1024-item
+    // slots
     int64_t gx = cdiv(items, (int64_t)kLanebitThreads);
     if (gx > 256) gx = 256;
+    unsigned long long *const words_arg = om_words_for(commit, rows * cols, gx);
     if (esz == 2)
       hipLaunchKernelGGL((measure_lanebit<2, 8>), dim3((unsigned)gx), dim3(kLanebitThreads), 0,
-                         stream, static_cast<const char *>(x), items, words, mask, counts, commit);
+                         stream, static_cast<const char *>(x), items, words, mask, counts, words_arg);
     else if (lv == 8)
       hipLaunchKernelGGL((measure_lanebit<4, 8>), dim3((unsigned)gx), dim3(kLanebitThreads), 0,
-                         stream, static_cast<const char *>(x), items, words, mask, counts, commit);
+                         stream, static_cast<const char *>(x), items, words, mask, counts, words_arg);
     else
       hipLaunchKernelGGL((measure_lanebit<4, 4>), dim3((unsigned)gx), dim3(kLanebitThreads), 0,
-                         stream, static_cast<const char *>(x), items, words, mask, counts, commit);
+                         stream, static_cast<const char *>(x), items, words, mask, counts, words_arg);
     SPAROA_LAUNCH_CHECK("measure_lanebit");
     return SPAROA_OK;
   }
   if (rowbit) {
     int64_t gx = cdiv(cdiv(rows, 8), (int64_t)kLanebitThreads);
     if (gx > 256) gx = 256;
+    unsigned long long *const words_arg = om_words_for(commit, rows * cols, gx);
     if (esz == 2)
       hipLaunchKernelGGL(measure_rowbit<2>, dim3((unsigned)gx), dim3(kLanebitThreads), 0, stream,
                          static_cast<const char *>(x), rows, (int)cols, words, mask, counts,
-                         commit);
+                         words_arg);
     else
       hipLaunchKernelGGL(measure_rowbit<4>, dim3((unsigned)gx), dim3(kLanebitThreads), 0, stream,
                          static_cast<const char *>(x), rows, (int)cols, words, mask, counts,
-                         commit);
+                         words_arg);
     SPAROA_LAUNCH_CHECK("measure_rowbit");
     return SPAROA_OK;
   }

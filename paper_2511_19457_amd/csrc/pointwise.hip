@@ -111,6 +111,38 @@ __global__ __launch_bounds__(kPwThreads, pw_waves(NB, R, KS)) void pointwise_ker
   // weight slice is staged (nothing before needs the decision)
   const RouteCountsReq rq = route_counts_request(a.route);
 
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc((void *)a.x, (short)0, a.x_bytes, kBufDword3);
+  const bool unit_stride = a.sh == 1 && a.sw == 1;
+
+  // activations of one tile: every k-step of the R pixel blocks (lane:
+  // pixel rl, channels 8g..8g+7 of each 32-wide k-step), straight loads
+  auto load_tile = [&](int tile, u32x4 (&bx)[R][KS]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int m = tile * P + (wave * R + r) * 16 + rl;
+      int pixel = m;
+      if (!unit_stride) {
+        const int mm = m < a.M ? m : 0;
+        int t1, ow, n, oh;
+        divmod_f(mm, a.Wo, a.inv_wo, t1, ow);
+        divmod_f(t1, a.Ho, a.inv_ho, n, oh);
+        pixel = (n * a.H + oh * a.sh) * a.W + ow * a.sw;
+      }
+      const int off = (pixel * a.K + 8 * g) * 2;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const bool ok = m < a.M && 32 * s + 8 * g < a.K;
+        bx[r][s] = __builtin_amdgcn_raw_buffer_load_b128(xr, ok ? off + 64 * s : (int)0x80000000,
+                                                          0, 0);
+      }
+    }
+  };
+
+  u32x4 cur[R][KS];
+  int tile = wg_in_slice;
+  if (tile < a.tiles) load_tile(tile, cur);   // in flight while the weights are staged
+
   // ---- weight slice -> LDS, zero past C_out and past K (16-byte vectors;
   // K % 8 == 0, so a vector never straddles two rows).  Eight independent
   // loads per thread in flight per round (addresses clamped, values masked).
@@ -148,8 +180,6 @@ __global__ __launch_bounds__(kPwThreads, pw_waves(NB, R, KS)) void pointwise_ker
       *a.route.path_out = (skip ? 1u : 0u) | ((uint32_t)a.route.bw_bit << 1);
   }
 
-  const __amdgpu_buffer_rsrc_t xr =
-      __builtin_amdgcn_make_buffer_rsrc((void *)a.x, (short)0, a.x_bytes, kBufDword3);
   const bool om = a.om_counts != nullptr;
   const int C8 = a.Cout / 8;
   uint32_t om_zeros = 0, om_nz = 0;
@@ -157,32 +187,6 @@ __global__ __launch_bounds__(kPwThreads, pw_waves(NB, R, KS)) void pointwise_ker
   const raw *bias = reinterpret_cast<const raw *>(a.bias);
   const raw *res = reinterpret_cast<const raw *>(a.residual);
   raw *y = reinterpret_cast<raw *>(a.y);
-  const bool unit_stride = a.sh == 1 && a.sw == 1;
-
-  // activations of one tile: every k-step of the R pixel blocks (lane:
-  // pixel rl, channels 8g..8g+7 of each 32-wide k-step), straight loads
-  auto load_tile = [&](int tile, u32x4 (&bx)[R][KS]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int m = tile * P + (wave * R + r) * 16 + rl;
-      int pixel = m;
-      if (!unit_stride) {
-        const int mm = m < a.M ? m : 0;
-        int t1, ow, n, oh;
-        divmod_f(mm, a.Wo, a.inv_wo, t1, ow);
-        divmod_f(t1, a.Ho, a.inv_ho, n, oh);
-        pixel = (n * a.H + oh * a.sh) * a.W + ow * a.sw;
-      }
-      const int off = (pixel * a.K + 8 * g) * 2;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const bool ok = m < a.M && 32 * s + 8 * g < a.K;
-        bx[r][s] = __builtin_amdgcn_raw_buffer_load_b128(xr, ok ? off + 64 * s : (int)0x80000000,
-                                                          0, 0);
-      }
-    }
-  };
-
   // This lane's output vectors of a pixel: 8 channels at c0 + 32 jp + 8 g per
   // block pair jp (one block alone: 4 channels at c0 + 4 g).
   constexpr int NP = NB == 1 ? 1 : NB / 2, CV = NB == 1 ? 4 : 8;
@@ -207,12 +211,8 @@ __global__ __launch_bounds__(kPwThreads, pw_waves(NB, R, KS)) void pointwise_ker
   const bool om_bytes = NB % 4 == 0 && a.om_mask && C8 % 8 == 0;
   const bool om_lds = a.om_mask && !om_bytes;
 
-  u32x4 cur[R][KS], nxt[R][KS];
+  u32x4 nxt[R][KS];
   vec_t rv[RES ? R : 1][RES ? NP : 1];
-  int tile = wg_in_slice;
-  if (tile < a.tiles) {
-    load_tile(tile, cur);
-  }
   for (; tile < a.tiles; tile += wgs_per_slice) {
     const int p0 = tile * P;
     const int next = tile + wgs_per_slice;
@@ -491,7 +491,6 @@ sparoa_status launch_pointwise(const sparoa_conv_desc &d, const void *x, const v
   a.route = route ? *route : DeviceRoute{nullptr, 0.0, 0, 0, nullptr};
   a.om_counts = om ? om->counts : nullptr;
   a.om_mask = om ? om->mask : nullptr;
-  a.om_words = om ? om->words : nullptr;
   a.om_mask_words = a.om_mask ? (a.M * (int64_t)(d.c_out / 8) + 31) / 32 : 0;   // null: counts only
   const unsigned lds = (unsigned)(c.nb * 16 * c.row_bytes);
   const bool res = residual != nullptr;
@@ -507,6 +506,7 @@ sparoa_status launch_pointwise(const sparoa_conv_desc &d, const void *x, const v
   if (per_slice < 1) per_slice = 1;
   if (per_slice > a.tiles) per_slice = a.tiles;
   const dim3 grid((unsigned)(per_slice * c.slices));
+  a.om_words = om ? om_words_for(om->words, (int64_t)a.M * a.Cout, grid.x) : nullptr;
   // (executed_blocks was zeroed by the caller, launch_gemm_conv)
   void *args[] = {&a};
   SPAROA_HIP_CHECK(hipLaunchKernel(fn, grid, dim3(kPwThreads), args, lds, stream));
