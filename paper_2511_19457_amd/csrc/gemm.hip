@@ -770,12 +770,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
   // their 16-byte vectors swizzled: slot = vector ^ f(row), so that the
   // operand reads of any 8 consecutive lanes hit distinct banks.  Pixel rows
   // are read 16 consecutive ones at a time, f = row & 7.  Channel rows are
-  // read in the order that leaves a lane 16 consecutive output channels
-  // (MFMA row 4 q + t of block b is channel 16 q + 4 b + t of its group of
-  // 64), f = (row >> 4 & 1) * 4 + (row & 3).
+  // read in the order that leaves a lane 8 consecutive output channels per
+  // block pair (MFMA row 4 q + t of block b is channel 32 (b / 2) + 8 q +
+  // 4 (b % 2) + t), f = (row >> 3 & 1) * 4 + (row & 3).
   const int lrow = lane >> 3;
   const int cgA = (lane & 7) ^ lrow;
-  const int cgB = (lane & 7) ^ ((((wave >> 1) & 1) << 2) | (lrow & 3));
+  const int cgB = (lane & 7) ^ (((wave & 1) << 2) | (lrow & 3));
 
   // ---- gathered pixels of this lane's A rows (fixed over the K loop).
   // Loads go through buffer descriptors: a 32-bit byte offset per lane, and
@@ -877,7 +877,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
     offA[ks] = (wm * WTM * 16 + rl) * ROW + 16 * ((4 * ks + g) ^ (rl & 7));
-    offB[ks] = (BM + wn * WTN * 16 + 16 * (rl >> 2) + (rl & 3)) * ROW + 16 * ((4 * ks + g) ^ fB);
+    offB[ks] = (BM + wn * WTN * 16 + 8 * (rl >> 2) + (rl & 3)) * ROW + 16 * ((4 * ks + g) ^ fB);
   }
   struct Operands {
     u32x4 a[2][WTM], b[2][WTN];   // of a chunk's two k-steps
@@ -889,7 +889,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
     const char *st = smem + slot * STAGE;
     if (v < WTN)
       o.b[ks][v] = *reinterpret_cast<const u32x4 *>(st + offB[ks] +
-                                                    (64 * (v >> 2) + 4 * (v & 3)) * ROW);
+                                                    (32 * (v >> 1) + 4 * (v & 1)) * ROW);
     else
       o.a[ks][v - WTN] = *reinterpret_cast<const u32x4 *>(st + offA[ks] + (v - WTN) * 16 * ROW);
   };
@@ -975,13 +975,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
     }
   }
 
-  // ---- epilogue, from registers: a lane holds channels 16 g + [0, 16) of
-  // each 64-channel group of pixel rl of its WTM pixel blocks -- two 16-byte
-  // vectors of bias, residual and output (four lanes of a pixel write 128
+  // ---- epilogue, from registers: a lane holds channels 32 p + 8 g + [0, 8)
+  // of each block pair p, of pixel rl of its WTM pixel blocks -- 16-byte
+  // vectors of bias, residual and output (four lanes of a pixel write 64
   // consecutive bytes).  The residual vectors are requested before the first
   // store (a load issued behind stores waits for them).
   const bool vec_n = N % 8 == 0;
-  const int mw = m0 + wm * WTM * 16 + rl, nw = n0 + wn * WTN * 16 + 16 * g;
+  const int mw = m0 + wm * WTM * 16 + rl, nw = n0 + wn * WTN * 16 + 8 * g;
   uint32_t om_zeros = 0, om_nz = 0;
   if (a.split > 1) {
 #pragma unroll
@@ -995,12 +995,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           const f32x4 v = acc[tm][4 * q + b];
+          const int c = 32 * (b >> 1) + 4 * (b & 1);
           if (vec_n) {
-            if (col + 4 * b < N) *reinterpret_cast<f32x4 *>(dst + 4 * b) = v;
+            if (col + c < N) *reinterpret_cast<f32x4 *>(dst + c) = v;
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (col + 4 * b + e < N) dst[4 * b + e] = v[e];
+              if (col + c + e < N) dst[c + e] = v[e];
           }
         }
       }
@@ -1019,7 +1020,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
       for (int b = 0; b < WTN; ++b)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int col = nw + 64 * (b >> 2) + 4 * (b & 3) + e;
+          const int col = nw + 32 * (b >> 1) + 4 * (b & 1) + e;
           if (col >= N) continue;
           float v = acc[tm][b][e];
           if (bias) v += E::to_f32(bias[col]);
@@ -1034,7 +1035,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
   for (int q = 0; q < NG; ++q)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int col = nw + 64 * q + 8 * h;
+      const int col = nw + 64 * q + 32 * h;
       bias_q[q][h] = uint4{0u, 0u, 0u, 0u};
       if (bias && col < N) bias_q[q][h] = *reinterpret_cast<const uint4 *>(bias + col);
     }
@@ -1045,7 +1046,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
       for (int q = 0; q < NG; ++q)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const int row = mw + 16 * tm, col = nw + 64 * q + 8 * h;
+          const int row = mw + 16 * tm, col = nw + 64 * q + 32 * h;
           res_q[tm][q][h] = uint4{0u, 0u, 0u, 0u};
           if (row < M && col < N)
             res_q[tm][q][h] =
@@ -1063,7 +1064,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
       uint32_t nzb[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int col = nw + 64 * q + 8 * h;
+        const int col = nw + 64 * q + 32 * h;
         const bool valid = row < M && col < N;
         float o[8];
 #pragma unroll
@@ -1098,13 +1099,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
         const uint64_t b0 = __ballot(nzb[0] != 0u), b1 = __ballot(nzb[1] != 0u);
         // rows past M still clear their bytes when they lie inside the
         // bitmap's last word (bits past the last block are 0)
-        const int byte = row * (N / 64) + (nw - 16 * g) / 64 + q;
+        const int byte = row * (N / 64) + (nw - 8 * g) / 64 + q;
         if (g == 0 && nw + 64 * q < N && byte < mbytes) {
           uint32_t v = 0;
 #pragma unroll
           for (int p = 0; p < 4; ++p)
-            v |= ((uint32_t)(b0 >> (rl + 16 * p)) & 1u) << (2 * p) |
-                 ((uint32_t)(b1 >> (rl + 16 * p)) & 1u) << (2 * p + 1);
+            v |= ((uint32_t)(b0 >> (rl + 16 * p)) & 1u) << p |
+                 ((uint32_t)(b1 >> (rl + 16 * p)) & 1u) << (4 + p);
           reinterpret_cast<uint8_t *>(a.om_mask)[byte] = (uint8_t)v;
         }
       }
