@@ -1115,6 +1115,330 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// Implicit GEMM of few tiles: small tiles whose waves split K.  Where a layer
+// has too few 64 x 64 tiles to fill the chip, its time is the chain of chunks
+// of one tile and, with K split over work-groups, a reduction launch.  Here a
+// tile is 16 TM x 16 TN outputs, small enough to give every CU one, and wave w
+// of a work-group takes chunks w, w + NW, ... of it: the wave's own ring of S
+// chunks in LDS (the loads of igemm_kernel), so the K loop has no barrier;
+// the NW partial tiles meet in LDS at the end, added in wave order.  A chunk
+// is 128 bytes of channels of one tap: 64 at 16 bits, 32 in fp32.
+// What bounds it is latency: launch, set-up, one memory round trip, a few
+// chunks, the reduction and the commit.
+// Skipping is by the rows the tiling query reports: a wave drops those of its
+// chunks whose gathered input is zero over the 64-row unit the tile lies in,
+// so the output equals the dense form's bit for bit.
+constexpr int kSkipRows = 64;
+
+template <int DT, int TM, int TN, int NW, int S, bool PART>
+__global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
+  using E = Elem<DT>;
+  using raw = typename E::raw;
+  constexpr int ESZ = E::size;
+  constexpr int NT = 64 * NW;
+  constexpr int BM = 16 * TM, BN = 16 * TN;
+  constexpr int C = 128 / ESZ;         // channels of a chunk
+  constexpr int ROW = 128;
+  constexpr int L = 2 * (TM + TN);     // loads of a chunk: 8 rows each
+  constexpr int STAGE = (BM + BN) * ROW;
+  constexpr int CS = BN + 4;           // fp32 row stride of a partial tile
+  constexpr int PART_BYTES = BM * CS * 4;
+  constexpr int ITEMS = BM * BN / 8;   // epilogue items: 8 channels of a pixel
+  constexpr int EIT = (ITEMS + NT - 1) / NT;
+  constexpr int RING = NW * S * STAGE, RED = NW * PART_BYTES;
+  static_assert(kSkipRows % BM == 0, "a tile lies in one skip unit");
+  static_assert(L * (S - 1) < 64, "vmcnt range");
+
+  __shared__ __attribute__((aligned(1024))) char smem[RING > RED ? RING : RED];
+  __shared__ uint32_t list[NW][(kMaxChunks2 + NW - 1) / NW];
+  __shared__ uint32_t nzvec[kMaxVecWords + 1];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (the set-up's kernel arguments in one round trip, as in igemm_kernel)
+  asm volatile("" ::"s"(a.M), "s"(a.N), "s"(a.K), "s"(a.H), "s"(a.W), "s"(a.Cin), "s"(a.Ho),
+               "s"(a.Wo), "s"(a.Kw), "s"(a.sh), "s"(a.sw), "s"(a.ph), "s"(a.pw), "s"(gridDim.x),
+               "s"(a.route.counts), "s"(a.route.path_out), "s"(a.om_counts), "s"(a.nchunks));
+  const bool om = a.om_counts != nullptr;
+  const RouteCountsReq rq = route_counts_request(a.route);
+  const TileId tl = tile_of(a);
+  const int m0 = tl.mt * BM, n0 = tl.nt * BN;
+  const int M = (int)a.M, N = (int)a.N, n = (int)a.nchunks;
+  const int H = (int)a.H, W = (int)a.W, Ho = (int)a.Ho, Wo = (int)a.Wo, Cin = (int)a.Cin;
+  const int kw = (int)a.Kw;
+
+  // ---- this lane's rows of the loads: load q of a chunk fills rows 8 q + l /
+  // 8, slot l % 8 holding vector (l % 8) ^ (row % 8)
+  const int lrow = lane >> 3, cg = (lane & 7) ^ lrow;
+  const u32x4 xr = buffer_words(a.x, a.x_bytes), wr = buffer_words(a.w, a.w_bytes);
+  int a_offb[2 * TM], b_offb[2 * TN];
+  uint32_t orow[2 * TM], ocol[2 * TM];  // bit r / s: kernel row r / column s outside the image
+#pragma unroll
+  for (int u = 0; u < 2 * TM; ++u) {
+    const int m = m0 + 8 * u + lrow;
+    int t1, ow, nn, oh;
+    divmod_small(m < M ? m : 0, Wo, a.inv_wo, t1, ow);
+    divmod_small(t1, Ho, a.inv_ho, nn, oh);
+    const int h0 = oh * (int)a.sh - (int)a.ph, w0 = ow * (int)a.sw - (int)a.pw;
+    a_offb[u] = ((nn * H + h0) * W + w0) * Cin * ESZ + 16 * cg;
+    orow[u] = ~taps_inside(h0, H, a.kh32, (int)a.dh, a.inv_dh);
+    ocol[u] = ~taps_inside(w0, W, kw, (int)a.dw, a.inv_dw);
+  }
+#pragma unroll
+  for (int u = 0; u < 2 * TN; ++u) {
+    const int jn = n0 + 8 * u + lrow;
+    b_offb[u] = (jn < N ? jn : 0) * (int)a.K * ESZ + 16 * cg;
+  }
+
+  // ---- this wave's walk (its own list: no barrier on the dense path)
+  uint32_t *const mine = list[wave];
+  const WalkGeom geom = walk_geom<ESZ>(a);
+  int nloc = n > wave ? (n - wave + NW - 1) / NW : 0;
+  for (int i = lane; i < nloc; i += 64) mine[i] = walk_entry<C, ESZ>(a, wave + NW * i);
+  bool use_list = a.mask != nullptr;
+  const int u0 = m0 / kSkipRows * kSkipRows;
+  const bool counts_here = tl.nt == 0 && u0 == m0;   // one tile per unit counts executed blocks
+  if (a.route.sample_zeros) {
+    use_list = split_route_skips(a, u0, kSkipRows);
+    if (!use_list && a.executed && counts_here && tid == 0)
+      atomicAdd(a.executed, (unsigned long long)n);  // a dense unit runs every chunk
+  } else {
+    if (a.route.counts) use_list = route_counts_skip(rq, a.route);
+    if (a.route.path_out && tl.tile == 0 && tid == 0)
+      *a.route.path_out = (a.route.counts && use_list ? 1u : 0u) | ((uint32_t)a.route.bw_bit << 1);
+  }
+  if (use_list) {
+    gather_nonzero_bits<NT>(a, u0, kSkipRows, nzvec);
+    int total = 0;
+    for (int base = 0; base < nloc; base += 64) {
+      const int i = base + lane, j = wave + NW * min(i, nloc - 1);
+      const bool nz = i < nloc && chunk_nonzero<C, PART>(a, nzvec, j);
+      const uint64_t bal = __ballot(nz);
+      const int before = __popcll(bal & ((1ull << lane) - 1ull));
+      if (nz) mine[total + before] = walk_entry<C, ESZ>(a, j);
+      total += __popcll(bal);
+    }
+    nloc = total;
+    if (lane == 0 && a.executed && counts_here && total)
+      atomicAdd(a.executed, (unsigned long long)total);
+  }
+  nloc = __builtin_amdgcn_readfirstlane(nloc);
+
+  // ---- the K loop
+  const uint32_t ring =
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + wave * (S * STAGE);
+  const char *const stages = smem + wave * (S * STAGE);
+  auto load_chunk = [&](int i, int slot) __attribute__((always_inline)) {
+    const WalkStep e = walk_step(geom, mine[i]);
+    const int cb2 = PART ? e.kofs % (Cin * ESZ) : 0;
+    const bool col = !PART || cb2 + cg * 16 < Cin * ESZ;   // channels past C_in read zero
+    const uint32_t dst = ring + slot * STAGE;
+#pragma unroll
+    for (int u = 0; u < 2 * TM; ++u) {
+      const uint32_t out = orow[u] << e.rsh | ocol[u] << e.ssh;
+      const uint32_t off = (uint32_t)(a_offb[u] + e.xofs) | (out & 0x80000000u);
+      load_to_lds(xr, dst + u * 1024, col ? (int)off : (int)0x80000000, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 2 * TN; ++u)
+      load_to_lds(wr, dst + BM * ROW + u * 1024, col ? b_offb[u] : (int)0x80000000, e.kofs);
+  };
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int g = lane >> 4, rl = lane & 15;
+  int opoff[2];   // operand offset of the chunk's two halves: row rl, vector 4 h + g
+#pragma unroll
+  for (int h = 0; h < 2; ++h) opoff[h] = rl * ROW + 16 * ((4 * h + g) ^ (rl & 7));
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+    if (s < nloc) load_chunk(s, s);
+
+  // (the epilogue's bias and residual vectors, behind the first chunks)
+  const bool vec_n = N % 8 == 0;
+  const raw *bias = reinterpret_cast<const raw *>(a.bias);
+  const raw *res = reinterpret_cast<const raw *>(a.residual);
+  raw *y = reinterpret_cast<raw *>(a.y);
+  constexpr int QV = ESZ / 2;   // 16-byte vectors of 8 elements
+  uint4 bias_q[EIT][QV], res_q[EIT][QV];
+#pragma unroll
+  for (int it = 0; it < EIT; ++it) {
+    const int q = tid + it * NT;
+    const int row = m0 + q / (BN / 8), col = n0 + q % (BN / 8) * 8;
+    const bool in = q < ITEMS && row < M && col < N && vec_n;
+#pragma unroll
+    for (int v = 0; v < QV; ++v) {
+      bias_q[it][v] = res_q[it][v] = uint4{0u, 0u, 0u, 0u};
+      if (bias && in)
+        bias_q[it][v] = *reinterpret_cast<const uint4 *>(bias + col + v * (16 / ESZ));
+      if (res && in)
+        res_q[it][v] =
+            *reinterpret_cast<const uint4 *>(res + (int64_t)row * N + col + v * (16 / ESZ));
+    }
+  }
+
+  int slot = 0;
+  for (int i = 0; i < nloc; ++i) {
+    // chunk i has landed when at most the newer chunks' loads are outstanding
+    // (and, waited for too, the epilogue vectors issued behind the first S)
+    wait_chunks<S - 1, L>(min(S - 1, nloc - 1 - i));
+    asm volatile("" ::: "memory");
+    const char *st = stages + slot * STAGE;
+    u32x4 fa[2][TM], fb[2][TN];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int b = 0; b < TM; ++b)
+        fa[h][b] = *reinterpret_cast<const u32x4 *>(st + opoff[h] + b * 16 * ROW);
+#pragma unroll
+      for (int b = 0; b < TN; ++b)
+        fb[h][b] = *reinterpret_cast<const u32x4 *>(st + opoff[h] + (BM + b * 16) * ROW);
+    }
+    if (i + S < nloc) {
+      __builtin_amdgcn_s_waitcnt(kLgkmcnt0);   // the stage is read: refill it
+      load_chunk(i + S, slot);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+          if constexpr (DT == SPAROA_BF16)
+            acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, fb[h][tn]), __builtin_bit_cast(bf16x8, fa[h][tm]),
+                acc[tm][tn], 0, 0, 0);
+          else if constexpr (DT == SPAROA_F16)
+            acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                __builtin_bit_cast(f16x8, fb[h][tn]), __builtin_bit_cast(f16x8, fa[h][tm]),
+                acc[tm][tn], 0, 0, 0);
+          else {
+            const f32x4 va = __builtin_bit_cast(f32x4, fa[h][tm]);
+            const f32x4 vb = __builtin_bit_cast(f32x4, fb[h][tn]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              acc[tm][tn] =
+                  __builtin_amdgcn_mfma_f32_16x16x4f32(vb[e], va[e], acc[tm][tn], 0, 0, 0);
+          }
+        }
+    slot = slot == S - 1 ? 0 : slot + 1;
+  }
+
+  // ---- the partial tiles meet in LDS, in the rings' place (a lane holds 4
+  // consecutive channels 4 g + [0, 4) of pixel rl of each block)
+  if (NW > 1) __syncthreads();
+  else asm volatile("" ::: "memory");
+  float *const red = reinterpret_cast<float *>(smem);
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn)
+      *reinterpret_cast<f32x4 *>(red + wave * (BM * CS) + (16 * tm + rl) * CS + 16 * tn + 4 * g) =
+          acc[tm][tn];
+  __syncthreads();
+  uint32_t om_zeros = 0, om_nz = 0;
+  const int parts = min(NW, n);   // waves past the last chunk hold zeros
+#pragma unroll
+  for (int it = 0; it < EIT; ++it) {
+    const int q = tid + it * NT;
+    if (q - lane >= ITEMS) break;   // whole waves
+    const int r = q / (BN / 8), c = q % (BN / 8) * 8;
+    const int row = m0 + r, col = n0 + c;
+    const bool valid = q < ITEMS && row < M && col < N;
+    f32x4 lo = f32x4{0.f, 0.f, 0.f, 0.f}, hi = lo;
+    if (valid) {
+      for (int w = 0; w < parts; ++w) {
+        lo += *reinterpret_cast<const f32x4 *>(red + w * (BM * CS) + r * CS + c);
+        hi += *reinterpret_cast<const f32x4 *>(red + w * (BM * CS) + r * CS + c + 4);
+      }
+    }
+    float o[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    if (!vec_n) {
+      if (valid) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (col + e >= N) break;
+          float v = o[e];
+          if (bias) v += E::to_f32(bias[col + e]);
+          if (res) v += E::to_f32(res[(int64_t)row * N + col + e]);
+          y[(int64_t)row * N + col + e] = E::from_f32(apply_act(v, a.act));
+        }
+      }
+      continue;   // (N % 8 == 0 whenever the output is measured)
+    }
+    raw t[8];
+    if (bias) {
+      __builtin_memcpy(t, bias_q[it], 8 * ESZ);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] += E::to_f32(t[e]);
+    }
+    if (res) {
+      __builtin_memcpy(t, res_q[it], 8 * ESZ);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] += E::to_f32(t[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = apply_act(o[e], a.act);
+    if constexpr (ESZ == 4) {
+      if (valid) {
+        float *d = reinterpret_cast<float *>(a.y) + (int64_t)row * N + col;
+        *reinterpret_cast<float4 *>(d) = make_float4(o[0], o[1], o[2], o[3]);
+        *reinterpret_cast<float4 *>(d + 4) = make_float4(o[4], o[5], o[6], o[7]);
+      }
+    } else {
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = E::pack2(o[2 * e], o[2 * e + 1]);
+      uint4 q4;
+      __builtin_memcpy(&q4, w, 16);
+      if (valid) *reinterpret_cast<uint4 *>(y + (int64_t)row * N + col) = q4;
+      if (om) {
+        const uint32_t nz = nonzeros16<4>(w);
+        om_zeros += valid ? 8u - nz : 0u;
+        const bool nzb = valid && nz != 0u;
+        om_nz += nzb ? 1u : 0u;
+        if (a.om_mask) {
+          // A pixel's BN / 8 bits of the bitmap: a byte of it, or bits of one or
+          // two words, set and cleared by atomics (each bit has one owner, so
+          // neither the order nor what the words held matters).
+          constexpr int LB = BN / 8;   // lanes (and bits) of a pixel's row
+          const uint64_t bal = __ballot(nzb), have = __ballot(valid);
+          const uint32_t bits = (uint32_t)(bal >> (lane & ~(LB - 1))) & ((1u << LB) - 1u);
+          const uint32_t own = (uint32_t)(have >> (lane & ~(LB - 1))) & ((1u << LB) - 1u);
+          if (LB == 8 && N % 64 == 0) {   // a byte of the bitmap: stored
+            if ((lane & (LB - 1)) == 0 && own)
+              reinterpret_cast<uint8_t *>(a.om_mask)[(int64_t)row * (N / 64) + col / 64] =
+                  (uint8_t)bits;
+          } else if ((lane & (LB - 1)) == 0 && own) {
+            const int64_t bit = (int64_t)row * (N / 8) + col / 8;
+            const int sh = (int)(bit & 31);
+            uint32_t *wd = a.om_mask + (bit >> 5);
+            const uint64_t set = (uint64_t)bits << sh, clr = (uint64_t)(own & ~bits) << sh;
+            if ((uint32_t)set) atomicOr(wd, (uint32_t)set);
+            if ((uint32_t)clr) atomicAnd(wd, ~(uint32_t)clr);
+            if ((uint32_t)(set >> 32)) atomicOr(wd + 1, (uint32_t)(set >> 32));
+            if ((uint32_t)(clr >> 32)) atomicAnd(wd + 1, ~(uint32_t)(clr >> 32));
+          }
+        }
+      }
+    }
+  }
+  if (om) {
+    if (a.om_mask && tl.tile == 0 && tid == 0) {   // bits past the last block are 0
+      const int64_t nb = (int64_t)M * (N / 8);
+      if (BN == 64 && N % 64 == 0) {
+        for (int64_t b = nb / 8; b & 3; ++b) reinterpret_cast<uint8_t *>(a.om_mask)[b] = 0;
+      } else if (nb & 31) {
+        atomicAnd(a.om_mask + (nb >> 5), (1u << (nb & 31)) - 1u);
+      }
+    }
+    om_commit(om_zeros, om_nz, a.om_counts, a.om_words, blockIdx.x, gridDim.x);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Direct MFMA conv for inputs with at most 4 channels (image stems: ResNet's
 // 7x7/2 and MobileNetV2's 3x3/2 over RGB), where the implicit GEMM's 8- or
 // 64-channel K chunks would be mostly padding and its gathers scalar.  A
@@ -1437,6 +1761,46 @@ bool dispatch_ig(int cfg, bool part, dim3 grid, hipStream_t st, const GemmArgs &
   return false;
 }
 
+// Tiles of the few-tile kernel (rows x columns); Long: 8 waves, Many: 2.
+enum LkCfg {
+  kLkNone, kLk16x16, kLk16x16Long, kLk16x32, kLk16x32Long, kLk16x64, kLk32x32, kLk32x64, kLk64x64,
+  kLk64x64Many
+};
+struct LkTile {
+  int cfg = kLkNone, bm = 0, bn = 0;
+};
+
+template <int DT, int TM, int TN, int NW, int S>
+void launch_lk(bool part, dim3 grid, hipStream_t st, const GemmArgs &a) {
+  if constexpr (DT != SPAROA_F32) {
+    if (part) {
+      hipLaunchKernelGGL((igemm_lk_kernel<DT, TM, TN, NW, S, true>), grid, dim3(64 * NW), 0, st, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((igemm_lk_kernel<DT, TM, TN, NW, S, false>), grid, dim3(64 * NW), 0, st, a);
+}
+
+template <int DT>
+bool dispatch_lk(int cfg, bool part, dim3 grid, hipStream_t st, const GemmArgs &a) {
+  switch (cfg) {
+    case kLk16x16: launch_lk<DT, 1, 1, 4, 4>(part, grid, st, a); return true;
+    case kLk16x16Long: launch_lk<DT, 1, 1, 8, 4>(part, grid, st, a); return true;
+    case kLk16x32: launch_lk<DT, 1, 2, 4, 4>(part, grid, st, a); return true;
+    case kLk16x32Long: launch_lk<DT, 1, 2, 8, 3>(part, grid, st, a); return true;
+    case kLk16x64: launch_lk<DT, 1, 4, 4, 3>(part, grid, st, a); return true;
+    case kLk32x32: launch_lk<DT, 2, 2, 2, 4>(part, grid, st, a); return true;
+    case kLk32x64: launch_lk<DT, 2, 4, 4, 3>(part, grid, st, a); return true;
+  }
+  if constexpr (DT == SPAROA_F32) {
+    switch (cfg) {
+      case kLk64x64: launch_lk<DT, 4, 4, 4, 2>(part, grid, st, a); return true;
+      case kLk64x64Many: launch_lk<DT, 4, 4, 2, 2>(part, grid, st, a); return true;
+    }
+  }
+  return false;
+}
+
 __global__ void set_u64(unsigned long long *p, unsigned long long v) { *p = v; }
 
 template <int DT, int TM, int TN, bool VEC, bool SKIP>
@@ -1716,6 +2080,52 @@ GemmTileChoice ig_choose(const Shape &s, int64_t c_in) {
   t.split_k = (int)split;
   return t;
 }
+
+// Tile of the few-tile kernel, or none.  The narrowest of 16 x 16, 16 x 32,
+// 16 x 64 and 32 x 64 of which there are at most 256, one per CU: their K loop
+// is a chain of memory round trips, so a second tile on a CU costs as much
+// again (fp16, K = 1024: 1024 x 512 16 x 64, 512 tiles, 9.5 us; 32 x 64, 256
+// tiles, 6.7).  Against the 64-row tiles with K split over work-groups and
+// their reduction (M x N x K, fp16): 784 x 128 x 1152 4.8 us and 7.9; 196 x
+// 256 x 1024 4.5 and 7.8; 49 x 512 x 4608 6.4 and 10.2; 196 x 1024 x 256 4.3
+// and 5.4; 2048 x 256 x 1024 6.7 and 8.0.  8 waves from 18 chunks (32: 5.1 and
+// 5.3 us with 4; 16: 4.6 and 4.5).  Under 4 chunks the 32 x 64 tile's four
+// waves have no work: 32 x 32 with two (2048 x 256 x 128 4.6 and 4.8).  Above
+// 512 chunks a wave's chain is longer than a split's (288 chunks 12.6 us and
+// 14.4, 0.24 and 0.19 us for each eight more).
+// fp32 has no other kernel with whole 128-byte chunks: 64 x 64 tiles beyond
+// these, four waves up to 256 tiles, else two (against the general kernel:
+// 1024^3 26.0 and 41.5 us; 2048^3 152 and 188; 6272 x 256 x 2304 86 and 121).
+LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice &t) {
+  LkTile l;
+  const bool f32 = d.dtype == SPAROA_F32;
+  const int64_t c = f32 ? kBK : kBK2, chunks = d.kh * d.kw * cdiv(d.c_in, c);
+  if (f32) {   // byte offsets below 2^31; the indices and lists as in ig_eligible
+    if (t.cfg || t.pointwise || t.small_c || d.groups != 1 || d.c_in % c) return l;
+    if (d.n * d.h * d.w * d.c_in >= ((int64_t)1 << 29) || s.N * s.K >= ((int64_t)1 << 29)) return l;
+    if (s.M >= ((int64_t)1 << 24) || d.kw > 32 || d.kh > 32 || chunks > kMaxChunks2) return l;
+    if (d.kh * d.kw * (d.c_in / 8) > (int64_t)kMaxVecWords * 32) return l;
+    if (cdiv(s.M, 64) * cdiv(s.N, 64) >= (int64_t)1 << 24) return l;
+  } else if (!t.cfg || chunks > 512) {
+    return l;
+  }
+  auto take = [&](int cfg, int bm, int bn) {
+    l.cfg = cfg;
+    l.bm = bm;
+    l.bn = bn;
+    return l;
+  };
+  auto tiles = [&](int bm, int bn) { return cdiv(s.M, bm) * cdiv(s.N, bn); };
+  const bool deep = chunks >= 18;
+  if (tiles(16, 16) <= 256) return take(deep ? kLk16x16Long : kLk16x16, 16, 16);
+  if (tiles(16, 32) <= 256) return take(deep ? kLk16x32Long : kLk16x32, 16, 32);
+  if (tiles(16, 64) <= 256) return take(kLk16x64, 16, 64);
+  if (tiles(32, 64) <= 256)
+    return chunks < 4 ? take(kLk32x32, 32, 32) : take(kLk32x64, 32, 64);
+  if (f32) return take(tiles(64, 64) <= 256 ? kLk64x64 : kLk64x64Many, 64, 64);
+  return l;
+}
+
 }  // namespace
 
 bool gemm_skip_supported(const sparoa_conv_desc &d) {
@@ -1853,7 +2263,10 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
   a.act = act;
   a.route = route ? *route : DeviceRoute{nullptr, 0.0, 0, 0, nullptr};
   if (!skip) a.route.counts = nullptr;   // no skip form to route to
-  const int64_t gz = cdiv(nchunks, a.chunks_per_split);
+  // the few-tile kernel splits K inside a work-group; the workspace that the
+  // query names is asked for all the same
+  const LkTile lk = lk_choose(d, s, t);
+  const int64_t splits = cdiv(nchunks, a.chunks_per_split), gz = lk.cfg ? 1 : splits;
   a.split = (int)gz;
   // the epilogue measures y when it writes y; with split-K the reduction does
   a.om_counts = om && gz == 1 ? om->counts : nullptr;
@@ -1861,7 +2274,7 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
   // grouped count commit when the caller gives the words
   unsigned long long *om_words = om ? om->words : nullptr;
   a.om_words = gz == 1 ? om_words : nullptr;
-  if (gz > 1 && ws_bytes < (size_t)gz * s.M * s.N * sizeof(float))
+  if (splits > 1 && ws_bytes < (size_t)splits * s.M * s.N * sizeof(float))
     return fail(SPAROA_ERR_WORKSPACE, "GEMM split-K workspace too small");
 
   if (executed) {
@@ -1880,8 +2293,9 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
     return launch_pointwise(d, x, w, bias, residual, act, y, skip, executed, stream, route, om);
   }
   dim3 grid((unsigned)cdiv(s.M, t.bm), (unsigned)cdiv(s.N, t.bn), (unsigned)gz);
-  if (t.cfg) {
-    const int64_t ntn = cdiv(s.N, t.bn), ntmn = cdiv(s.M, t.bm) * ntn;
+  if (t.cfg || lk.cfg) {
+    const int64_t ntn = cdiv(s.N, lk.cfg ? lk.bn : t.bn);
+    const int64_t ntmn = cdiv(s.M, lk.cfg ? lk.bm : t.bm) * ntn;
     if (ntmn * gz >= (int64_t)1 << 24)
       return fail(SPAROA_ERR_UNSUPPORTED, "GEMM: 2^24 tiles or more");
     grid = dim3((unsigned)(ntmn * gz));
@@ -1902,7 +2316,13 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
   }
   bool ok = false;
   const bool part = d.c_in % kBK2 != 0;   // a tap's last chunk is partial
-  if (t.cfg) {
+  if (lk.cfg) {
+    switch (d.dtype) {
+      case SPAROA_BF16: ok = dispatch_lk<SPAROA_BF16>(lk.cfg, part, grid, stream, a); break;
+      case SPAROA_F16: ok = dispatch_lk<SPAROA_F16>(lk.cfg, part, grid, stream, a); break;
+      case SPAROA_F32: ok = dispatch_lk<SPAROA_F32>(lk.cfg, part, grid, stream, a); break;
+    }
+  } else if (t.cfg) {
     switch (d.dtype) {
       case SPAROA_BF16:
         ok = dispatch_ig<SPAROA_BF16>(t.cfg, part, grid, stream, a);
