@@ -31,6 +31,26 @@ inline unsigned long long *om_words_for(unsigned long long *words, int64_t numel
                          : words;
 }
 
+// Sum of v over the 64 lanes of a wave, in lane 63.  Six adds whose operand
+// moves between lanes in the vector unit (row shifts, then row broadcasts):
+// the same sum by shuffles goes through LDS six times, one latency each.  (The
+// commit is the tail of every measuring kernel: with the parts below read at
+// once it takes 1.45 us of a 14 x 14 layer, 1.7 with shuffles and one LDS read
+// per wave; the rest is the atomics.  8 groups instead of 16: 0.05 to 0.3 us
+// slower, 4: 0.3 to 0.7.)
+__device__ __forceinline__ uint32_t wave_sum_63(uint32_t v) {
+#define SPAROA_DPP_ADD(ctrl, rows) \
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, true)
+  SPAROA_DPP_ADD(0x111, 0xf);   // row_shr:1, :2, :4, :8
+  SPAROA_DPP_ADD(0x112, 0xf);
+  SPAROA_DPP_ADD(0x114, 0xf);
+  SPAROA_DPP_ADD(0x118, 0xf);
+  SPAROA_DPP_ADD(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+  SPAROA_DPP_ADD(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef SPAROA_DPP_ADD
+  return v;
+}
+
 // Adds a work-group's zero count and nonzero-block count into counts
 // (zero_blocks starts at nb).  Same-address atomics serialise device-wide
 // (13-17 ns per work-group measured with one atomic per counter), so with
@@ -44,23 +64,25 @@ inline unsigned long long *om_words_for(unsigned long long *words, int64_t numel
 // are left untouched).
 __device__ __forceinline__ void om_commit(uint32_t zeros, uint32_t nz, sparoa_counts *counts,
                                           unsigned long long *words, int64_t b, int64_t nwg) {
-  __shared__ uint32_t part[2][16];
+  __shared__ __attribute__((aligned(16))) uint32_t part[2][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    zeros += __shfl_xor(zeros, o, 64);
-    nz += __shfl_xor(nz, o, 64);
-  }
-  if (lane == 0) {
+  zeros = wave_sum_63(zeros);
+  nz = wave_sum_63(nz);
+  if (lane == 63) {
     part[0][wave] = zeros;
     part[1][wave] = nz;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
+    // every slot is read (in a few wide reads, all in flight at once), those
+    // past the last wave's dropped
     unsigned long long z = 0, n = 0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) {
-      z += part[0][i];
-      n += part[1][i];
+    const int waves = (int)(blockDim.x >> 6);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t pz = part[0][i], pn = part[1][i];
+      z += i < waves ? pz : 0u;
+      n += i < waves ? pn : 0u;
     }
     // small grids commit directly: the ticket's returning atomic is a memory
     // round trip on every work-group's path (about 1 us), more than up to 64
