@@ -70,6 +70,9 @@ struct GemmArgs {
   // column groups of the tile walk: gw column tiles a group (the last one
   // lastw), gt = row tiles x gw
   int gw32, gt32, lastw32;
+  // first output row of the launch, and the rows that skip together (the
+  // reported tile rows; both multiples of them)
+  int row0, skip_rows;
   float inv_gt, inv_gw, inv_lastw;
   int act;
   int split;
@@ -758,8 +761,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
   const RouteCountsReq rq = route_counts_request(a.route);
   const TileId tl = tile_of(a);
   const int zsplit = tl.zsplit;
-  const int m0 = tl.mt * BM, n0 = tl.nt * BN;
-  const bool first_tile = tl.tile == 0, first_col = tl.nt == 0;
+  const int m0 = a.row0 + tl.mt * BM, n0 = tl.nt * BN;
+  // a skip unit of several tiles is counted by its first
+  const int unit = (int)a.skip_rows, u0 = m0 & ~(unit - 1);
+  const bool first_tile = tl.tile == 0, first_col = tl.nt == 0 && u0 == m0;
   const int cps = (int)a.chunks_per_split;
   const int c_begin = zsplit * cps;
   const int c_end = min(c_begin + cps, (int)a.nchunks);
@@ -814,7 +819,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
   for (int i = tid; i < count; i += NT) list[i] = walk_entry<kBK2, 2>(a, c_begin + i);
   bool use_list = a.mask != nullptr;
   if (a.route.sample_zeros) {
-    use_list = split_route_skips(a, m0, BM);
+    use_list = split_route_skips(a, u0, unit);
     if (!use_list && a.executed && first_col && tid == 0 && count)
       atomicAdd(a.executed, (unsigned long long)count);  // a dense tile runs every chunk
   } else {
@@ -823,7 +828,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
       *a.route.path_out = (a.route.counts && use_list ? 1u : 0u) | ((uint32_t)a.route.bw_bit << 1);
   }
   if (use_list) {
-    gather_nonzero_bits<NT>(a, m0, BM, nzvec);
+    gather_nonzero_bits<NT>(a, u0, unit, nzvec);
     if (wave == 0) {
       int total = 0;
       for (int base = c_begin; base < c_end; base += 64) {
@@ -1126,9 +1131,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
 // What bounds it is latency: launch, set-up, one memory round trip, a few
 // chunks, the reduction and the commit.
 // Skipping is by the rows the tiling query reports: a wave drops those of its
-// chunks whose gathered input is zero over the 64-row unit the tile lies in,
+// chunks whose gathered input is zero over the unit the tile lies in,
 // so the output equals the dense form's bit for bit.
-constexpr int kSkipRows = 64;
 
 template <int DT, int TM, int TN, int NW, int S, bool PART>
 __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
@@ -1146,7 +1150,6 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
   constexpr int ITEMS = BM * BN / 8;   // epilogue items: 8 channels of a pixel
   constexpr int EIT = (ITEMS + NT - 1) / NT;
   constexpr int RING = NW * S * STAGE, RED = NW * PART_BYTES;
-  static_assert(kSkipRows % BM == 0, "a tile lies in one skip unit");
   static_assert(L * (S - 1) < 64, "vmcnt range");
 
   __shared__ __attribute__((aligned(1024))) char smem[RING > RED ? RING : RED];
@@ -1162,7 +1165,7 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
   const bool om = a.om_counts != nullptr;
   const RouteCountsReq rq = route_counts_request(a.route);
   const TileId tl = tile_of(a);
-  const int m0 = tl.mt * BM, n0 = tl.nt * BN;
+  const int m0 = a.row0 + tl.mt * BM, n0 = tl.nt * BN;
   const int M = (int)a.M, N = (int)a.N, n = (int)a.nchunks;
   const int H = (int)a.H, W = (int)a.W, Ho = (int)a.Ho, Wo = (int)a.Wo, Cin = (int)a.Cin;
   const int kw = (int)a.Kw;
@@ -1196,10 +1199,10 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
   int nloc = n > wave ? (n - wave + NW - 1) / NW : 0;
   for (int i = lane; i < nloc; i += 64) mine[i] = walk_entry<C, ESZ>(a, wave + NW * i);
   bool use_list = a.mask != nullptr;
-  const int u0 = m0 / kSkipRows * kSkipRows;
+  const int unit = a.skip_rows, u0 = m0 & ~(unit - 1);
   const bool counts_here = tl.nt == 0 && u0 == m0;   // one tile per unit counts executed blocks
   if (a.route.sample_zeros) {
-    use_list = split_route_skips(a, u0, kSkipRows);
+    use_list = split_route_skips(a, u0, unit);
     if (!use_list && a.executed && counts_here && tid == 0)
       atomicAdd(a.executed, (unsigned long long)n);  // a dense unit runs every chunk
   } else {
@@ -1208,7 +1211,7 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
       *a.route.path_out = (a.route.counts && use_list ? 1u : 0u) | ((uint32_t)a.route.bw_bit << 1);
   }
   if (use_list) {
-    gather_nonzero_bits<NT>(a, u0, kSkipRows, nzvec);
+    gather_nonzero_bits<NT>(a, u0, unit, nzvec);
     int total = 0;
     for (int base = 0; base < nloc; base += 64) {
       const int i = base + lane, j = wave + NW * min(i, nloc - 1);
@@ -2126,6 +2129,19 @@ LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice
   return l;
 }
 
+// Rows of the first launch of a layer in 128 x 256 tiles.  One such tile
+// fills a CU, so a few tiles beyond whole rounds of 256 cost a round of their
+// own; where the rest is at most half a round, its rows go to a second launch
+// in the tiles that suit so many rows.  Measured (M = 128 tiles' rows x 256 x
+// K, bf16, one launch and two): 256 + 16 tiles of K = 2304 59.2 and 45.7 us,
+// + 64 58.5 and 52.1, + 128 60.4 and 57.3, + 160 74.0 and 89.2; K = 768,
+// 512 + 16 47.4 and 41.6, + 128 48.6 and 47.5, + 160 49.2 and 53.2.
+int64_t ig_head_rows(const Shape &s, const GemmTileChoice &t) {
+  if (t.cfg != kIg128x256) return s.M;
+  const int64_t ntn = cdiv(s.N, t.bn), tiles = cdiv(s.M, t.bm) * ntn, rest = tiles % 256;
+  if (tiles < 256 || rest == 0 || rest > 128) return s.M;
+  return (tiles - rest) / ntn * t.bm;
+}
 }  // namespace
 
 bool gemm_skip_supported(const sparoa_conv_desc &d) {
@@ -2292,52 +2308,60 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
                                        nullptr, nullptr, nullptr};
     return launch_pointwise(d, x, w, bias, residual, act, y, skip, executed, stream, route, om);
   }
-  dim3 grid((unsigned)cdiv(s.M, t.bm), (unsigned)cdiv(s.N, t.bn), (unsigned)gz);
+  bool ok = false;
   if (t.cfg || lk.cfg) {
-    const int64_t ntn = cdiv(s.N, lk.cfg ? lk.bn : t.bn);
-    const int64_t ntmn = cdiv(s.M, lk.cfg ? lk.bm : t.bm) * ntn;
-    if (ntmn * gz >= (int64_t)1 << 24)
-      return fail(SPAROA_ERR_UNSUPPORTED, "GEMM: 2^24 tiles or more");
-    grid = dim3((unsigned)(ntmn * gz));
-    a.om_words = om_words_for(a.om_words, s.M * s.N, ntmn);
-    const int64_t gw = cdiv(ntn, ig_column_groups(ntn, a.x_bytes, a.w_bytes));
-    const int64_t gt = ntmn / ntn * gw, lastw = ntn - (cdiv(ntn, gw) - 1) * gw;
-    a.ntn32 = (int)ntn;
-    a.ntmn32 = (int)ntmn;
-    a.gw32 = (int)gw;
-    a.gt32 = (int)gt;
-    a.lastw32 = (int)lastw;
-    a.inv_ntmn = 1.0f / (float)ntmn;
-    a.inv_gt = 1.0f / (float)gt;
-    a.inv_gw = 1.0f / (float)gw;
-    a.inv_lastw = 1.0f / (float)lastw;
+    const bool part = d.c_in % kBK2 != 0;   // a tap's last chunk is partial
     a.cpt32 = (int)cdiv(d.c_in, t.kchunk);
     a.inv_cpt = 1.0f / (float)a.cpt32;
-  }
-  bool ok = false;
-  const bool part = d.c_in % kBK2 != 0;   // a tap's last chunk is partial
-  if (lk.cfg) {
-    switch (d.dtype) {
-      case SPAROA_BF16: ok = dispatch_lk<SPAROA_BF16>(lk.cfg, part, grid, stream, a); break;
-      case SPAROA_F16: ok = dispatch_lk<SPAROA_F16>(lk.cfg, part, grid, stream, a); break;
-      case SPAROA_F32: ok = dispatch_lk<SPAROA_F32>(lk.cfg, part, grid, stream, a); break;
+    a.skip_rows = t.bm;
+    // rows [row0, row0 + rows) in tiles of the few-tile kernel or of u.cfg
+    unsigned long long *const words = a.om_words;
+    auto launch_rows = [&](int64_t row0, int64_t rows, const LkTile &l, const GemmTileChoice &u) {
+      const int64_t ntn = cdiv(s.N, l.cfg ? l.bn : u.bn);
+      const int64_t ntmn = cdiv(rows, l.cfg ? l.bm : u.bm) * ntn;
+      if (ntmn * gz >= (int64_t)1 << 24) return false;   // refused below
+      const dim3 grid((unsigned)(ntmn * gz));
+      a.row0 = (int)row0;
+      a.om_words = om_words_for(words, s.M * s.N, ntmn);
+      const int64_t gw = cdiv(ntn, ig_column_groups(ntn, a.x_bytes, a.w_bytes));
+      const int64_t gt = ntmn / ntn * gw, lastw = ntn - (cdiv(ntn, gw) - 1) * gw;
+      a.ntn32 = (int)ntn;
+      a.ntmn32 = (int)ntmn;
+      a.gw32 = (int)gw;
+      a.gt32 = (int)gt;
+      a.lastw32 = (int)lastw;
+      a.inv_ntmn = 1.0f / (float)ntmn;
+      a.inv_gt = 1.0f / (float)gt;
+      a.inv_gw = 1.0f / (float)gw;
+      a.inv_lastw = 1.0f / (float)lastw;
+      switch (d.dtype) {
+        case SPAROA_BF16:
+          return l.cfg ? dispatch_lk<SPAROA_BF16>(l.cfg, part, grid, stream, a)
+                       : dispatch_ig<SPAROA_BF16>(u.cfg, part, grid, stream, a);
+        case SPAROA_F16:
+          return l.cfg ? dispatch_lk<SPAROA_F16>(l.cfg, part, grid, stream, a)
+                       : dispatch_ig<SPAROA_F16>(u.cfg, part, grid, stream, a);
+        default:
+          return l.cfg != 0 && dispatch_lk<SPAROA_F32>(l.cfg, part, grid, stream, a);
+      }
+    };
+    const int64_t head = lk.cfg || gz > 1 ? s.M : ig_head_rows(s, t);
+    ok = launch_rows(0, head, lk, t);
+    if (ok && head < s.M) {
+      Shape rest = s;
+      rest.M = s.M - head;
+      const GemmTileChoice u = ig_choose(rest, d.c_in);
+      ok = launch_rows(head, rest.M, lk_choose(d, rest, u), u);
     }
-  } else if (t.cfg) {
+  } else {
+    const dim3 grid((unsigned)cdiv(s.M, t.bm), (unsigned)cdiv(s.N, t.bn), (unsigned)gz);
     switch (d.dtype) {
-      case SPAROA_BF16:
-        ok = dispatch_ig<SPAROA_BF16>(t.cfg, part, grid, stream, a);
-        break;
-      case SPAROA_F16:
-        ok = dispatch_ig<SPAROA_F16>(t.cfg, part, grid, stream, a);
-        break;
-      default: break;
+      case SPAROA_BF16: ok = dispatch<SPAROA_BF16>(t.bm, t.bn, vec, skip, grid, stream, a); break;
+      case SPAROA_F16: ok = dispatch<SPAROA_F16>(t.bm, t.bn, vec, skip, grid, stream, a); break;
+      case SPAROA_F32: ok = dispatch<SPAROA_F32>(t.bm, t.bn, vec, skip, grid, stream, a); break;
     }
-  } else switch (d.dtype) {
-    case SPAROA_BF16: ok = dispatch<SPAROA_BF16>(t.bm, t.bn, vec, skip, grid, stream, a); break;
-    case SPAROA_F16: ok = dispatch<SPAROA_F16>(t.bm, t.bn, vec, skip, grid, stream, a); break;
-    case SPAROA_F32: ok = dispatch<SPAROA_F32>(t.bm, t.bn, vec, skip, grid, stream, a); break;
   }
-  if (!ok) return fail(SPAROA_ERR_UNSUPPORTED, "GEMM tile shape");
+  if (!ok) return fail(SPAROA_ERR_UNSUPPORTED, "GEMM tile shape, or 2^24 tiles or more");
   SPAROA_LAUNCH_CHECK("gemm_kernel");
   const SplitReduceJob job{d.dtype, a.partial, gz > 1 ? (int)gz : 0, s.M, s.N, bias, residual,
                            act, y, om && gz > 1 ? om->counts : nullptr,
