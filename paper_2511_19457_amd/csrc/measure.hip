@@ -19,6 +19,7 @@
 // few hundred work-groups that loop over the tensor.
 #include "commit.h"
 #include "common.h"
+#include "dtype.h"
 
 namespace sparoa {
 namespace {
@@ -61,8 +62,9 @@ __device__ __forceinline__ void wg_commit(uint64_t zeros, uint64_t nonzero, spar
                                           uint64_t *sample_zeros) {
   __shared__ unsigned long long part[2][NT / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t wz = wave_sum(zeros), wn = wave_sum(nonzero);
-  if (lane == 0) {
+  // (a wave's counts are below 2^32, as om_commit's)
+  const uint32_t wz = wave_sum_63((uint32_t)zeros), wn = wave_sum_63((uint32_t)nonzero);
+  if (lane == 63) {
     part[0][wave] = wz;
     part[1][wave] = wn;
   }
@@ -143,12 +145,29 @@ __device__ __forceinline__ uint32_t nonzero_bits(const char *p) {
 // The V elements of one lanebit item (one block of 1 x V): a 16-byte vector,
 // or two of them for fp32 blocks of 8 (32 contiguous bytes per lane).
 template <int ESZ, int V>
-__device__ __forceinline__ uint32_t item_nonzero_bits(const char *p) {
-  if constexpr (V * ESZ == 32)
-    return nonzero_bits<ESZ, V / 2>(p) | (nonzero_bits<ESZ, V / 2>(p + 16) << (V / 2));
-  else
-    return nonzero_bits<ESZ, V>(p);
-}
+struct LanebitItem {
+  uint4 q[V * ESZ / 16] = {};
+  __device__ __forceinline__ void load(const char *p) {
+#pragma unroll
+    for (int i = 0; i < V * ESZ / 16; ++i) q[i] = *reinterpret_cast<const uint4 *>(p + 16 * i);
+  }
+  // Nonzero elements (+0 and -0 are zero).  Counted, not collected bit by bit:
+  // 14 instructions per 16 bytes of 16-bit elements instead of about 35.
+  __device__ __forceinline__ uint32_t nonzeros() const {
+    uint32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < V * ESZ / 16; ++i) {
+      const uint32_t w[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
+      if constexpr (ESZ == 2) {
+        n += nonzeros16<4>(w);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) n += min(w[e] & 0x7fffffffu, 1u);
+      }
+    }
+    return n;
+  }
+};
 
 // grid = (x: work-groups per sample, y: samples).  Sample s covers rows
 // [s*rs, s*rs + rs); its block rows are numbered s*nbr_s + local index.
@@ -225,46 +244,50 @@ __global__ __launch_bounds__(kThreads) void measure_main(
 // are two whole bitmap words.  The wave ballots its bits and two lanes store
 // the words: no atomics, and the bitmap needs no clearing.  The grid's slots
 // start at multiples of 64 items, which keeps the words aligned.
-constexpr int kLanebitThreads = 1024;  // one work-group per CU, 16 waves
-constexpr int kLanebitUnroll = 4;
+// Two slots in flight per wave: the waves overlap each other's loads, and a
+// small tensor's waves have one slot (51 MB, preset, 256 work-groups: 12.7 us
+// with 2, 14.3 with 4; 0.2 MB 2.9 and 3.0; with every slot processed whether
+// or not it holds items, and bits collected one by one, 15.2 and 4.0, and 8
+// slots 16.9 and 6.4).
+constexpr int kLanebitThreads = 1024;  // 16 waves
+constexpr int kLanebitUnroll = 2;
 
-// Work-group `bid` of `nblk` measuring one tensor.
+// Work-group `bid` of `nblk` measuring one tensor.  A wave loads the slots that
+// it has items in, all in flight, and skips the others.  mask null: counts only
+// (words 0).
 template <int ESZ, int V>
 __device__ __forceinline__ void lanebit_pass(const char *__restrict__ x, int64_t items,
                                              int64_t words, uint32_t *__restrict__ mask,
                                              sparoa_counts *counts, int64_t bid, int64_t nblk,
                                              unsigned long long *commit = nullptr) {
-  constexpr int NT = kLanebitThreads;
+  constexpr int NT = kLanebitThreads, U = kLanebitUnroll;
   const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t slot = nblk * NT;
-  uint64_t zeros = 0, nonzero = 0;
-  for (int64_t base = bid * NT; base < items; base += slot * kLanebitUnroll) {
-    // unconditional loads (items past the end re-read the last item and are
-    // masked), so all kLanebitUnroll stay in flight
-    uint32_t nz[kLanebitUnroll];
+  uint32_t zeros = 0, nonzero = 0;
+  for (int64_t base = bid * NT + wave * 64; base < items; base += slot * U) {
+    LanebitItem<ESZ, V> it[U];
+    // (lanes past the end of the last slot re-read the last item, masked below)
 #pragma unroll
-    for (int u = 0; u < kLanebitUnroll; ++u) {
-      const int64_t item = base + u * slot + threadIdx.x;
-      nz[u] = item_nonzero_bits<ESZ, V>(x + min(item, items - 1) * (V * ESZ));
-    }
+    for (int u = 0; u < U; ++u)
+      if (base + u * slot < items) it[u].load(x + min(base + u * slot + lane, items - 1) * (V * ESZ));
 #pragma unroll
-    for (int u = 0; u < kLanebitUnroll; ++u) {
-      const bool valid = base + u * slot + threadIdx.x < items;
-      nz[u] = valid ? nz[u] : 0u;
-      zeros += valid ? (uint64_t)(V - __popc(nz[u])) : 0ull;
-    }
-#pragma unroll
-    for (int u = 0; u < kLanebitUnroll; ++u) {
-      const uint64_t bal = __ballot(nz[u] != 0u);
-      const int64_t w0 = (base + u * slot + (threadIdx.x & ~63)) >> 5;
+    for (int u = 0; u < U; ++u) {
+      if (base + u * slot >= items) break;
+      const bool valid = base + u * slot + lane < items;
+      const uint32_t nz = it[u].nonzeros();
+      zeros += valid ? V - nz : 0u;
+      const uint64_t bal = __ballot(valid && nz != 0u);
+      const int64_t w0 = (base + u * slot) >> 5;
       if (lane == 0 && w0 < words) mask[w0] = (uint32_t)bal;
       if (lane == 32 && w0 + 1 < words) mask[w0 + 1] = (uint32_t)(bal >> 32);
-      nonzero += lane == 0 ? (uint64_t)__popcll(bal) : 0ull;
+      nonzero += (uint32_t)__popcll(bal);   // (the wave's: the same in every lane)
     }
   }
+  nonzero = lane == 0 ? nonzero : 0u;
   // with commit words: ticketed commits over 16 addresses instead of one
   // same-address atomic per counter per work-group
-  if (commit) om_commit((uint32_t)zeros, (uint32_t)nonzero, counts, commit, bid, nblk);
+  if (commit) om_commit(zeros, nonzero, counts, commit, bid, nblk);
   else wg_commit<NT>(zeros, nonzero, counts, nullptr);
 }
 
@@ -387,30 +410,30 @@ __global__ __launch_bounds__(1024) void measure_lanebit_wg(const char *__restric
   constexpr int NT = 1024, U = 8;
   __shared__ unsigned long long part[2][NT / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint64_t zeros = 0, nonzero = 0;
-  for (int64_t base = 0; base < items; base += (int64_t)NT * U) {
-    uint32_t nz[U];
+  uint32_t zeros = 0, nonzero = 0;
+  for (int64_t base = 64 * __builtin_amdgcn_readfirstlane(wave); base < items;
+       base += (int64_t)NT * U) {
+    LanebitItem<ESZ, V> it[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {  // unconditional loads, masked past the end
-      const int64_t item = base + u * NT + threadIdx.x;
-      nz[u] = item_nonzero_bits<ESZ, V>(x + min(item, items - 1) * (V * ESZ));
-    }
+    for (int u = 0; u < U; ++u)   // as in lanebit_pass
+      if (base + u * NT < items) it[u].load(x + min(base + u * NT + lane, items - 1) * (V * ESZ));
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t w0 = (base + u * NT + (threadIdx.x & ~63)) >> 5;
-      const bool valid = base + u * NT + threadIdx.x < items;
-      const uint32_t b = valid ? nz[u] : 0u;
-      zeros += valid ? (uint64_t)(V - __popc(b)) : 0ull;
-      const uint64_t bal = __ballot(b != 0u);
+      if (base + u * NT >= items) break;
+      const int64_t w0 = (base + u * NT) >> 5;
+      const bool valid = base + u * NT + lane < items;
+      const uint32_t nz = it[u].nonzeros();
+      zeros += valid ? V - nz : 0u;
+      const uint64_t bal = __ballot(valid && nz != 0u);
       if (lane == 0 && w0 < words) mask[w0] = (uint32_t)bal;
       if (lane == 32 && w0 + 1 < words) mask[w0 + 1] = (uint32_t)(bal >> 32);
-      nonzero += lane == 0 ? (uint64_t)__popcll(bal) : 0ull;
+      nonzero += (uint32_t)__popcll(bal);
     }
   }
-  const uint64_t wz = wave_sum(zeros), wn = wave_sum(nonzero);
-  if (lane == 0) {
+  const uint32_t wz = wave_sum_63(zeros);
+  if (lane == 63) {
     part[0][wave] = wz;
-    part[1][wave] = wn;
+    part[1][wave] = nonzero;   // the same in every lane
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -565,6 +588,22 @@ void launch_main(dim3 grid, hipStream_t st, const void *x, int64_t cols, int64_t
 
 }  // namespace
 
+// Work-groups of a lanebit pass: one item per lane at the least.  With commit
+// words up to two per CU (a commit is one returning atomic spread over 16
+// addresses, two above 2^27 elements; 51 MB 12.3 us with 512, 12.7 with 256).
+// Without them each work-group's two same-address atomics take their turn, 28
+// ns, behind the pass: about sqrt(items) / 7 work-groups balance the two
+// (6.4 MB: 96 7.8 us, 256 10.4, 32 10.3; 25.7 MB: 192 12.2, 256 13.0, 96 13.8).
+int64_t lanebit_grid(int64_t items, bool commit) {
+  int64_t gx = cdiv(items, (int64_t)kLanebitThreads);
+  if (gx > 512) gx = 512;
+  if (!commit) {
+    if (gx > 256) gx = 256;
+    while (gx > 1 && 49 * gx * gx > items) --gx;
+  }
+  return gx;
+}
+
 bool measure_groupable(const MeasureJob &j) {
   const int vw = 16 / (int)elem_size(j.dt);
   return j.mask && j.cols % vw == 0 && j.block_rows == 1 && j.block_cols == vw;
@@ -625,8 +664,7 @@ sparoa_status launch_measure_counts8(const void *x, sparoa_dtype dt, int64_t row
     SPAROA_LAUNCH_CHECK("measure_lanebit_wg");
     return SPAROA_OK;
   }
-  int64_t gx = cdiv(items, (int64_t)kLanebitThreads);
-  if (gx > 256) gx = 256;
+  const int64_t gx = lanebit_grid(items, commit_words != nullptr);
   unsigned long long *cw =
       om_words_for(reinterpret_cast<unsigned long long *>(commit_words), rows * cols, gx);
   if (h)
@@ -704,13 +742,7 @@ sparoa_status launch_measure(const void *x, sparoa_dtype dt, int64_t rows, int64
 
   if (lanebit) {
     const int64_t items = rows * (cols / lv);
-    // one work-group per CU where the tensor fills them (one item per lane
-    // at the least); with commit words a work-group's commit costs one
-    // returning atomic spread over 16 addresses (two above 2^27 elements), so
-    // a small tensor is spread over as many compute units as it has 1024-item
-    // slots
-    int64_t gx = cdiv(items, (int64_t)kLanebitThreads);
-    if (gx > 256) gx = 256;
+    const int64_t gx = lanebit_grid(items, commit != nullptr);
     unsigned long long *const words_arg = om_words_for(commit, rows * cols, gx);
     if (esz == 2)
       hipLaunchKernelGGL((measure_lanebit<2, 8>), dim3((unsigned)gx), dim3(kLanebitThreads), 0,
