@@ -246,9 +246,11 @@ def profile_summary(d, copy_mib):
         kib = {}
         for c, rows_c in per.items():
             if mfma:   # per operator: its GEMM and its share of the grouped measurement
-                ops = sum(1 for n, _ in rows_c if "igemm_kernel<" in n)    # and reduction
+                # and reduction, either implicit-GEMM kernel
+                ops = sum(1 for n, _ in rows_c if "igemm_kernel<" in n or "igemm_lk_kernel<" in n)
                 tot_c = sum(v for n, v in rows_c if any(k in n for k in (
-                    "measure_init", "measure_lanebit", "igemm_kernel<", "split_reduce")))
+                    "measure_init", "measure_lanebit", "igemm_kernel<", "igemm_lk_kernel<",
+                    "split_reduce")))
             else:      # one launch = one grouped self-measuring streaming-FC dispatch
                 sel = [v for n, v in rows_c if "fc_bw_measured_group<" in n]
                 ops, tot_c = len(sel), sum(sel)

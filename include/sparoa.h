@@ -395,8 +395,9 @@ sparoa_status sparoa_fc_routed(const sparoa_fc_desc *desc, const sparoa_threshol
  *   y_commit (nullable): SPAROA_COMMIT_WORDS_BYTES of device memory that
  *   must be all zero on entry and is all zero again when the call's kernels
  *   finish (a caller resets it with y_counts).  The fused form then commits
- *   its counts through 8 ticketed words per counter (one atomic per
- *   work-group on a word of its group; the work-group completing a group
+ *   its counts through ticketed words (one atomic per work-group on its
+ *   group's word, of 16 groups with both counts in one word, or of 8 with a
+ *   word per count from 2^27 elements up; the work-group completing a group
  *   adds the group's total to y_counts and clears the word) instead of one
  *   same-address atomic per work-group on y_counts.  NULL: direct commits,
  *   same counts.  Calls that overlap in time must not share y_commit.

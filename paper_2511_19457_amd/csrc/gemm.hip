@@ -535,8 +535,9 @@ __global__ __launch_bounds__(256) void split_reduce_group(ReduceGroup g) {
 // offset past the descriptor's range and lands as zeros.  One barrier per
 // chunk; a wave reads a chunk's MFMA operands from LDS, and sends the loads
 // that refill the stage freed by the barrier, between the MFMAs of the chunk
-// before.  The MFMA's rows are channels, so a lane ends with 16 consecutive
-// output channels of a pixel and the epilogue needs no LDS.
+// before.  The MFMA's rows are channels, so a lane ends with 8 consecutive
+// output channels of a pixel per block pair, four lanes with 32, and the
+// epilogue needs no LDS.
 // Bounds, measured with the other parts switched off (4096^3 fp16, 128 x 256:
 // 117 us): MFMAs alone 97 us (1.6 PFLOP/s with its start and end), loads
 // alone 95 us (17 TB/s out of the L2s); small tiles are bound by the loads
@@ -544,7 +545,8 @@ __global__ __launch_bounds__(256) void split_reduce_group(ReduceGroup g) {
 // chunks through registers, with two barriers' worth of LDS writes and an
 // epilogue through LDS: 4096^3 155 -> 117 us; 2048 x 768 x 3072 31 -> 19 us;
 // 3 x 3 512 -> 512 at 7 x 7, N = 32 29 -> 18 us; 3 x 3 256 -> 256 at 56 x 56,
-// N = 32 164 -> 137 us; K = 64 alone (start and epilogue), 4096 x 4096 20 ->
+// N = 32 164 -> 137 us (about 16 less with the rows past whole rounds apart,
+// ig_head_rows); K = 64 alone (start and epilogue), 4096 x 4096 20 ->
 // 12 us.  The ring's depth, beyond what one chunk's MFMAs cover, and more
 // waves of smaller tiles change nothing; branches and scalar arithmetic in
 // the loop did (a step written with guards: 20 % slower).
@@ -2069,7 +2071,10 @@ GemmTileChoice ig_choose(const Shape &s, int64_t c_in) {
   const int64_t tl = tiles(t.bm, 64), nchunks = chunks;
   int64_t split = 1;
   if (tl < 192) {   // (64 x 64 tiles: the wider ones are taken from 192 on)
-    // about one work-group per CU: more splits cost more partial traffic than
+    // The workspace that the query names, asked for also where the few-tile
+    // kernel takes the layer (lk_choose) and leaves it unused; the rest are
+    // layers of more than 256 tiles of 32 x 64, or of more than 512 chunks.
+    // About one work-group per CU: more splits cost more partial traffic than
     // they gain (FC 64 x 4096 x 4096: split 4 15.1 us, split 8 17.8 us)
     split = cdiv(256, tl);
     if (split > 8) split = 8;
