@@ -2145,7 +2145,9 @@ int64_t ig_head_rows(const Shape &s, const GemmTileChoice &t) {
   if (t.cfg != kIg128x256) return s.M;
   const int64_t ntn = cdiv(s.N, t.bn), tiles = cdiv(s.M, t.bm) * ntn, rest = tiles % 256;
   if (tiles < 256 || rest == 0 || rest > 128) return s.M;
-  return (tiles - rest) / ntn * t.bm;
+  // (whole rows of tiles: none where one row has more tiles than the rounds)
+  const int64_t head = (tiles - rest) / ntn * t.bm;
+  return head > 0 ? head : s.M;
 }
 }  // namespace
 
