@@ -2136,18 +2136,22 @@ LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice
 
 // Rows of the first launch of a layer in 128 x 256 tiles.  One such tile
 // fills a CU, so a few tiles beyond whole rounds of 256 cost a round of their
-// own; where the rest is at most half a round, its rows go to a second launch
-// in the tiles that suit so many rows.  Measured (M = 128 tiles' rows x 256 x
-// K, bf16, one launch and two): 256 + 16 tiles of K = 2304 59.2 and 45.7 us,
-// + 64 58.5 and 52.1, + 128 60.4 and 57.3, + 160 74.0 and 89.2; K = 768,
-// 512 + 16 47.4 and 41.6, + 128 48.6 and 47.5, + 160 49.2 and 53.2.
+// own; where few enough are left, their rows go to a second launch in the
+// tiles that suit so many rows.  The first launch takes whole rows of tiles
+// within the whole rounds, so what is left is more than tiles % 256 where the
+// columns' tiles do not divide 256, and everything where one row has more
+// tiles than the rounds hold.  The line lies at up to 128 left, without 65 to
+// 79 (these take 260 to 316 128 x 64 tiles, more than one a CU).  One launch
+// and two, bf16, M x N x K in us, with the tiles left: 3328 x 3072 x 2304 60
+// 59.9 and 53.4; 384 x 22016 x 4096 86 93.1 and 82.1; 6528 x 3072 x 1024 108
+// 57.5 and 56.7; 512 x 18944 x 1024 74 34.9 and 36.5; 1024 x 11008 x 768 129
+// 30.9 and 35.1; 256 x 43520 x 4096 170 134 and 192.
 int64_t ig_head_rows(const Shape &s, const GemmTileChoice &t) {
   if (t.cfg != kIg128x256) return s.M;
-  const int64_t ntn = cdiv(s.N, t.bn), tiles = cdiv(s.M, t.bm) * ntn, rest = tiles % 256;
-  if (tiles < 256 || rest == 0 || rest > 128) return s.M;
-  // (whole rows of tiles: none where one row has more tiles than the rounds)
-  const int64_t head = (tiles - rest) / ntn * t.bm;
-  return head > 0 ? head : s.M;
+  const int64_t ntn = cdiv(s.N, t.bn), tiles = cdiv(s.M, t.bm) * ntn;
+  const int64_t head = (tiles - tiles % 256) / ntn, left = tiles - head * ntn;
+  const bool few = left <= 64 || (left >= 80 && left <= 128);
+  return head > 0 && left > 0 && few ? head * t.bm : s.M;
 }
 }  // namespace
 

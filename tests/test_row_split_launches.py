@@ -64,3 +64,24 @@ def test_no_launch_is_empty(launches, dt, path):
     for call, (err, got) in zip(calls, launches(calls)):
         assert not err and got, (call, err)
         assert all(x and y and z for _, x, y, z in got), (call, got)
+
+
+# m, n and the 128 x 256 tiles of the first launch (0: one launch in all), by
+# the tiles that whole rows of tiles within whole rounds leave over
+SPLITS = [(33024, 256, 256), (3328, 3072, 252), (384, 22016, 172), (6528, 3072, 504),
+          (65536 + 128 * 128, 256, 512), (65536, 256, 0), (32768 + 64 * 128, 256, 256), (32768 + 80 * 128, 256, 256),
+          (32768 + 65 * 128, 256, 0), (32768 + 79 * 128, 256, 0), (512, 18944, 0),
+          (1024, 11008, 0), (32768 + 129 * 128, 256, 0), (256, 43520, 0), (384, 50432, 0),
+          (32768, 256, 0), (128, 81920, 0)]
+
+
+def test_rows_split_by_the_tiles_left(launches):
+    calls = [[m, 1024, n, 2, 0] for m, n, _ in SPLITS]
+    for (m, n, head), (err, got) in zip(SPLITS, launches(calls)):
+        assert not err, (m, n, err)
+        grids = [x for name, x, _, _ in got if "igemm" in name]
+        tiles = -(-m // 128) * -(-n // 256)
+        if head:
+            assert len(grids) == 2 and grids[0] == head and "2ELi4ELi4ELi4" in got[0][0], (m, n, got)
+        else:
+            assert grids == [tiles], (m, n, got)
