@@ -990,6 +990,54 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
   const bool vec_n = N % 8 == 0;
   const int mw = m0 + wm * WTM * 16 + rl, nw = n0 + wn * WTN * 16 + 8 * g;
   uint32_t om_zeros = 0, om_nz = 0;
+  const raw *bias = reinterpret_cast<const raw *>(a.bias);
+  const raw *res = reinterpret_cast<const raw *>(a.residual);
+  raw *y = reinterpret_cast<raw *>(a.y);
+  // Output rows that start anywhere (N % 8 != 0): a wave's blocks pass through
+  // LDS in the ring's place, 16 pixels x 64 channels at a time, so that its
+  // lanes store 64 consecutive channels element by element.  (Stored by the
+  // lanes that hold them, a store touched 16 rows: bf16 8619 x 1308 x 64 50 us,
+  // 3000 x 1308 x 1024 48; this way 27.5 and 32.)
+  if (!vec_n) {
+    constexpr int TS = 64 + 4;   // row stride: four rows of blocks hit distinct banks
+    static_assert(NW * 16 * TS * 4 <= S * STAGE, "the ring's place");
+    __syncthreads();   // every wave has read its last stage
+    float *const mine = reinterpret_cast<float *>(smem) + wave * (16 * TS);
+    float *const part = a.split > 1 ? a.partial + (int64_t)zsplit * M * N : nullptr;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      const int col = n0 + wn * WTN * 16 + 64 * q + lane;
+      const float bf = !part && bias && col < N ? E::to_f32(bias[col]) : 0.f;
+#pragma unroll
+      for (int tm = 0; tm < WTM; ++tm) {
+        const int row0 = m0 + wm * WTM * 16 + 16 * tm;
+        raw rv[16];
+        if (res && !part) {   // before the stores: a load issued behind them waits
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            rv[r] = row0 + r < M && col < N ? res[(int64_t)(row0 + r) * N + col] : (raw)0;
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          *reinterpret_cast<f32x4 *>(mine + rl * TS + 32 * (b >> 1) + 8 * g + 4 * (b & 1)) =
+              acc[tm][4 * q + b];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float v = mine[r * TS + lane];
+          if (row0 + r >= M || col >= N) continue;
+          const int64_t o = (int64_t)(row0 + r) * N + col;
+          if (part) {
+            part[o] = v;
+          } else {
+            if (bias) v += bf;
+            if (res) v += E::to_f32(rv[r]);
+            y[o] = E::from_f32(apply_act(v, a.act));
+          }
+        }
+      }
+    }
+    return;   // (N % 64 == 0 whenever the output is measured)
+  }
   if (a.split > 1) {
 #pragma unroll
     for (int tm = 0; tm < WTM; ++tm) {
@@ -1001,41 +1049,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
         float *dst = a.partial + ((int64_t)zsplit * M + row) * N + col;
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-          const f32x4 v = acc[tm][4 * q + b];
           const int c = 32 * (b >> 1) + 4 * (b & 1);
-          if (vec_n) {
-            if (col + c < N) *reinterpret_cast<f32x4 *>(dst + c) = v;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (col + c + e < N) dst[c + e] = v[e];
-          }
+          if (col + c < N) *reinterpret_cast<f32x4 *>(dst + c) = acc[tm][4 * q + b];
         }
       }
     }
     return;
-  }
-  const raw *bias = reinterpret_cast<const raw *>(a.bias);
-  const raw *res = reinterpret_cast<const raw *>(a.residual);
-  raw *y = reinterpret_cast<raw *>(a.y);
-  if (!vec_n) {
-#pragma unroll
-    for (int tm = 0; tm < WTM; ++tm) {
-      const int row = mw + 16 * tm;
-      if (row >= M) continue;
-#pragma unroll
-      for (int b = 0; b < WTN; ++b)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int col = nw + 32 * (b >> 1) + 4 * (b & 1) + e;
-          if (col >= N) continue;
-          float v = acc[tm][b][e];
-          if (bias) v += E::to_f32(bias[col]);
-          if (res) v += E::to_f32(res[(int64_t)row * N + col]);
-          y[(int64_t)row * N + col] = E::from_f32(apply_act(v, a.act));
-        }
-    }
-    return;   // (N % 64 == 0 whenever the output is measured)
   }
   uint4 bias_q[NG][2], res_q[WTM][NG][2];
 #pragma unroll
@@ -1343,8 +1362,37 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
       *reinterpret_cast<f32x4 *>(red + wave * (BM * CS) + (16 * tm + rl) * CS + 16 * tn + 4 * g) =
           acc[tm][tn];
   __syncthreads();
+  // Output rows that start anywhere: consecutive lanes take consecutive
+  // channels element by element, each its own channel throughout (fp32 4200 x
+  // 324 x 64 16.2 us with 8 channels a lane, 14.2 so).
+  if (!vec_n) {
+    static_assert(NT % BN == 0, "a lane's channel");
+    constexpr int RS = NT / BN, PER = (BM + RS - 1) / RS, U = PER < 8 ? PER : 8;
+    const int c = tid % BN, col = n0 + c;
+    const float bf = bias && col < N ? E::to_f32(bias[col]) : 0.f;
+    for (int i0 = 0; i0 < PER; i0 += U) {
+      float v[U], rf[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {   // the loads before the stores
+        const int r = tid / BN + (i0 + u) * RS;
+        const bool valid = r < BM && m0 + r < M && col < N;
+        rf[u] = res && valid ? E::to_f32(res[(int64_t)(m0 + r) * N + col]) : 0.f;
+        v[u] = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v[u] += red[w * (BM * CS) + min(r, BM - 1) * CS + c];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = tid / BN + (i0 + u) * RS;
+        if (bias) v[u] += bf;
+        if (res) v[u] += rf[u];
+        if (r < BM && m0 + r < M && col < N)
+          y[(int64_t)(m0 + r) * N + col] = E::from_f32(apply_act(v[u], a.act));
+      }
+    }
+    return;   // (N % 8 == 0 whenever the output is measured)
+  }
   uint32_t om_zeros = 0, om_nz = 0;
-  const int parts = min(NW, n);   // waves past the last chunk hold zeros
 #pragma unroll
   for (int it = 0; it < EIT; ++it) {
     const int q = tid + it * NT;
@@ -1354,25 +1402,13 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
     const bool valid = q < ITEMS && row < M && col < N;
     f32x4 lo = f32x4{0.f, 0.f, 0.f, 0.f}, hi = lo;
     if (valid) {
-      for (int w = 0; w < parts; ++w) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {   // (waves without a chunk hold zeros)
         lo += *reinterpret_cast<const f32x4 *>(red + w * (BM * CS) + r * CS + c);
         hi += *reinterpret_cast<const f32x4 *>(red + w * (BM * CS) + r * CS + c + 4);
       }
     }
     float o[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    if (!vec_n) {
-      if (valid) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if (col + e >= N) break;
-          float v = o[e];
-          if (bias) v += E::to_f32(bias[col + e]);
-          if (res) v += E::to_f32(res[(int64_t)row * N + col + e]);
-          y[(int64_t)row * N + col + e] = E::from_f32(apply_act(v, a.act));
-        }
-      }
-      continue;   // (N % 8 == 0 whenever the output is measured)
-    }
     raw t[8];
     if (bias) {
       __builtin_memcpy(t, bias_q[it], 8 * ESZ);
