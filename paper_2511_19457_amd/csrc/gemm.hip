@@ -2125,6 +2125,32 @@ GemmTileChoice ig_choose(const Shape &s, int64_t c_in) {
   return t;
 }
 
+// The tile of a few-tile layer that also writes a bitmap of its output.  Tiles
+// narrower than 64 channels set and clear their bits by atomics, 32 of them on
+// every word with 16 channels a tile, 16 with 32, and these end the kernel.
+// Where they cost more than the wider tile's longer chain of chunks, the next
+// tile up with the same number of waves (the same sums, bit for bit): rows
+// that share words (under 256 channels), long rows (1024 up), and grids of 33
+// to 64 work-groups, whose commits go straight to the counters.  Routed and
+// measured, bf16, M x N x K in us, narrow and wide (and 64 x 64 tiles): 400 x
+// 64 x 64 8.5, 5.9 (6.5); 196 x 128 x 512 9.0, 6.7 (8.7); 784 x 64 x 2304 10.7,
+// 8.7 (12.0); 16 x 2048 x 64 8.2, 6.0 (6.8); 49 x 256 x 256 7.0, 6.1 (7.4);
+// elsewhere 196 x 256 x 512 6.8, 7.3 (8.7); 100 x 512 x 1088 7.6, 8.3 (11.4);
+// one row of tiles 1 x 64 x 1088 6.5, 7.2 (10.6).
+LkTile lk_bitmap_tile(LkTile l, const Shape &s) {
+  const int64_t wgs = cdiv(s.M, l.bm) * cdiv(s.N, l.bn);
+  const bool wide = s.N < 256 ? s.M > 16 : s.N >= 1024 || (wgs > 32 && wgs <= 64);
+  if (!wide) return l;
+  if (l.cfg == kLk16x16 || l.cfg == kLk16x32) {
+    l.cfg = kLk16x64;
+    l.bn = 64;
+  } else if (l.cfg == kLk16x16Long) {
+    l.cfg = kLk16x32Long;
+    l.bn = 32;
+  }
+  return l;
+}
+
 // Tile of the few-tile kernel, or none.  The narrowest of 16 x 16, 16 x 32,
 // 16 x 64 and 32 x 64 of which there are at most 256, one per CU: their K loop
 // is a chain of memory round trips, so a second tile on a CU costs as much
@@ -2140,7 +2166,7 @@ GemmTileChoice ig_choose(const Shape &s, int64_t c_in) {
 // fp32 has no other kernel with whole 128-byte chunks: 64 x 64 tiles beyond
 // these, four waves up to 256 tiles, else two (against the general kernel:
 // 1024^3 26.0 and 41.5 us; 2048^3 152 and 188; 6272 x 256 x 2304 86 and 121).
-LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice &t) {
+LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice &t, bool bitmap) {
   LkTile l;
   const bool f32 = d.dtype == SPAROA_F32;
   const int64_t c = f32 ? kBK : kBK2, chunks = d.kh * d.kw * cdiv(d.c_in, c);
@@ -2157,7 +2183,7 @@ LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice
     l.cfg = cfg;
     l.bm = bm;
     l.bn = bn;
-    return l;
+    return bitmap ? lk_bitmap_tile(l, s) : l;
   };
   auto tiles = [&](int bm, int bn) { return cdiv(s.M, bm) * cdiv(s.N, bn); };
   const bool deep = chunks >= 18;
@@ -2328,7 +2354,8 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
   if (!skip) a.route.counts = nullptr;   // no skip form to route to
   // the few-tile kernel splits K inside a work-group; the workspace that the
   // query names is asked for all the same
-  const LkTile lk = lk_choose(d, s, t);
+  const bool bitmap = om && om->mask;
+  const LkTile lk = lk_choose(d, s, t, bitmap);
   const int64_t splits = cdiv(nchunks, a.chunks_per_split), gz = lk.cfg ? 1 : splits;
   a.split = (int)gz;
   // the epilogue measures y when it writes y; with split-K the reduction does
@@ -2398,7 +2425,7 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
       Shape rest = s;
       rest.M = s.M - head;
       const GemmTileChoice u = ig_choose(rest, d.c_in);
-      ok = launch_rows(head, rest.M, lk_choose(d, rest, u), u);
+      ok = launch_rows(head, rest.M, lk_choose(d, rest, u, bitmap), u);
     }
   } else {
     const dim3 grid((unsigned)cdiv(s.M, t.bm), (unsigned)cdiv(s.N, t.bn), (unsigned)gz);
