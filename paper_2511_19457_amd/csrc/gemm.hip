@@ -818,8 +818,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
   // tile's own samples (split execution), by the device route, or because the
   // host chose the skip path (a bitmap and neither of them).
   int count = c_end - c_begin;
-  for (int i = tid; i < count; i += NT) list[i] = walk_entry<kBK2, 2>(a, c_begin + i);
   bool use_list = a.mask != nullptr;
+  if (!use_list || a.route.counts || a.route.sample_zeros)   // (a dense walk is possible)
+    for (int i = tid; i < count; i += NT) list[i] = walk_entry<kBK2, 2>(a, c_begin + i);
   if (a.route.sample_zeros) {
     use_list = split_route_skips(a, u0, unit);
     if (!use_list && a.executed && first_col && tid == 0 && count)
@@ -1218,8 +1219,9 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
   uint32_t *const mine = list[wave];
   const WalkGeom geom = walk_geom<ESZ>(a);
   int nloc = n > wave ? (n - wave + NW - 1) / NW : 0;
-  for (int i = lane; i < nloc; i += 64) mine[i] = walk_entry<C, ESZ>(a, wave + NW * i);
   bool use_list = a.mask != nullptr;
+  if (!use_list || a.route.counts || a.route.sample_zeros)   // (a dense walk is possible)
+    for (int i = lane; i < nloc; i += 64) mine[i] = walk_entry<C, ESZ>(a, wave + NW * i);
   const int unit = a.skip_rows, u0 = m0 & ~(unit - 1);
   const bool counts_here = tl.nt == 0 && u0 == m0;   // one tile per unit counts executed blocks
   if (a.route.sample_zeros) {
