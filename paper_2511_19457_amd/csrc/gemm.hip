@@ -621,13 +621,16 @@ __device__ __forceinline__ TileId tile_of(const GemmArgs &a) {
 
 // Chunk j of the walk (C channels of ESZ bytes of one tap) as its loads need
 // it: 31 - r | 31 - s << 5 | kofs / 16 << 10, with the kernel row r and column
-// s of its tap and its byte offset kofs < 2^18 in a weight row.
-template <int C, int ESZ>
+// s of its tap and its byte offset kofs < 2^18 in a weight row; PART: bit 31
+// marks the last chunk of a tap (C_in % C != 0: the partial one).
+template <int C, int ESZ, bool PART>
 __device__ __forceinline__ uint32_t walk_entry(const GemmArgs &a, int j) {
   int t, cb, r, sx;
   divmod_small(j, a.cpt32, a.inv_cpt, t, cb);
   divmod_small(t, (int)a.Kw, a.inv_kw, r, sx);
-  return (uint32_t)((31 - r) | (31 - sx) << 5 | ((t * (int)a.Cin + cb * C) * ESZ / 16) << 10);
+  const uint32_t e =
+      (uint32_t)((31 - r) | (31 - sx) << 5 | ((t * (int)a.Cin + cb * C) * ESZ / 16) << 10);
+  return PART && cb == a.cpt32 - 1 ? e | 0x80000000u : e;
 }
 // A walk entry read as scalars (it is the same in every lane).  xofs: byte
 // offset of the chunk's channels from a row's first gathered pixel, from kofs
@@ -635,6 +638,7 @@ __device__ __forceinline__ uint32_t walk_entry(const GemmArgs &a, int j) {
 struct WalkStep {
   int kofs, xofs;
   uint32_t rsh, ssh;   // 31 - r, 31 - s: moves tap bit r / s to bit 31
+  uint32_t last;       // PART: all ones in a tap's last chunk, else 0
 };
 struct WalkGeom {
   uint32_t dr, ds, base;
@@ -647,12 +651,14 @@ __device__ __forceinline__ WalkGeom walk_geom(const GemmArgs &a) {
   g.base = 31u * (g.dr + g.ds);
   return g;
 }
+template <bool PART>
 __device__ __forceinline__ WalkStep walk_step(const WalkGeom &g, uint32_t entry) {
   const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)entry);
   WalkStep w;
   w.rsh = e & 31u;
   w.ssh = e >> 5 & 31u;
-  w.kofs = (int)(e >> 10 << 4);
+  w.last = PART ? (uint32_t)((int)e >> 31) : 0u;
+  w.kofs = (int)((PART ? e & 0x7fffffffu : e) >> 10 << 4);
   w.xofs = (int)((uint32_t)w.kofs + g.base - w.rsh * g.dr - w.ssh * g.ds);
   return w;
 }
@@ -820,7 +826,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
   int count = c_end - c_begin;
   bool use_list = a.mask != nullptr;
   if (!use_list || a.route.counts || a.route.sample_zeros)   // (a dense walk is possible)
-    for (int i = tid; i < count; i += NT) list[i] = walk_entry<kBK2, 2>(a, c_begin + i);
+    for (int i = tid; i < count; i += NT) list[i] = walk_entry<kBK2, 2, PART>(a, c_begin + i);
   if (a.route.sample_zeros) {
     use_list = split_route_skips(a, u0, unit);
     if (!use_list && a.executed && first_col && tid == 0 && count)
@@ -839,7 +845,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
         const bool nz = j < c_end && chunk_nonzero<kBK2, PART>(a, nzvec, min(j, c_end - 1));
         const uint64_t bal = __ballot(nz);
         const int before = __popcll(bal & ((1ull << lane) - 1ull));
-        if (nz) list[total + before] = walk_entry<kBK2, 2>(a, j);
+        if (nz) list[total + before] = walk_entry<kBK2, 2, PART>(a, j);
         total += __popcll(bal);
       }
       if (lane == 0) {
@@ -855,21 +861,22 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
   // ---- the K loop ----------------------------------------------------------
   const uint32_t ring =
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + wave * 1024;
+  // PART: bit 31 where this lane's 8 channels of a tap's last chunk lie past
+  // C_in (zero on both sides).  (With the chunk's place in its tap found by an
+  // integer remainder at every load 1700 x 320 x 440 took 8.1 us, 7.8 so.)
+  const int tail = PART ? (Cin - (a.cpt32 - 1) * kBK2) * 2 : ROW;
+  const uint32_t pastA = cgA * 16 < tail ? 0u : 0x80000000u;
+  const uint32_t pastB = cgB * 16 < tail ? 0u : 0x80000000u;
   // load u of one chunk's L (A rows, then B rows) into the stage at LDS
   // address dst; an offset with bit 31 set is out of range
   auto load_part = [&](const WalkStep &e, uint32_t dst, int u) __attribute__((always_inline)) {
-    // PART: a lane's 8 channels of the chunk exist (channels past C_in in
-    // the last chunk of a tap read zero on both sides)
-    const int cb2 = PART ? e.kofs % (Cin * 2) : 0;   // bytes into the tap's channels
     if (u < AV) {
-      const uint32_t out = orow[u] << e.rsh | ocol[u] << e.ssh;
-      uint32_t off = (uint32_t)(a_offb[u] + e.xofs) | (out & 0x80000000u);
-      if (PART && cb2 + cgA * 16 >= Cin * 2) off = 0x80000000u;
+      const uint32_t out = orow[u] << e.rsh | ocol[u] << e.ssh | (pastA & e.last);
+      const uint32_t off = (uint32_t)(a_offb[u] + e.xofs) | (out & 0x80000000u);
       load_to_lds(xr, dst + u * (NW * 1024), (int)off, 0);
     } else {
-      const bool colB = !PART || cb2 + cgB * 16 < Cin * 2;
       load_to_lds(wr, dst + BM * ROW + (u - AV) * (NW * 1024),
-                  colB ? b_offb[u - AV] : (int)0x80000000, e.kofs);
+                  b_offb[u - AV] | (int)(pastB & e.last), e.kofs);
     }
   };
 
@@ -930,7 +937,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
     constexpr bool STEADY = decltype(steady)::value;
     const bool more = STEADY || i + 1 < n, refill = STEADY || i + S < n;
     const uint32_t dst = ring + slot * STAGE;
-    const WalkStep e = walk_step(geom, next);
+    const WalkStep e = walk_step<PART>(geom, next);
     if (more) {
       if constexpr (STEADY) wait_chunks<S - 2, L>(S - 2);
       else wait_chunks<S - 2, L>(min(S - 2, n - 2 - i));
@@ -958,7 +965,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
 #pragma unroll
     for (int s = 0; s < S; ++s)
       if (s < n) {
-        const WalkStep e = walk_step(geom, list[s]);
+        const WalkStep e = walk_step<PART>(geom, list[s]);
 #pragma unroll
         for (int u = 0; u < L; ++u) load_part(e, ring + s * STAGE, u);
       }
@@ -1221,7 +1228,7 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
   int nloc = n > wave ? (n - wave + NW - 1) / NW : 0;
   bool use_list = a.mask != nullptr;
   if (!use_list || a.route.counts || a.route.sample_zeros)   // (a dense walk is possible)
-    for (int i = lane; i < nloc; i += 64) mine[i] = walk_entry<C, ESZ>(a, wave + NW * i);
+    for (int i = lane; i < nloc; i += 64) mine[i] = walk_entry<C, ESZ, PART>(a, wave + NW * i);
   const int unit = a.skip_rows, u0 = m0 & ~(unit - 1);
   const bool counts_here = tl.nt == 0 && u0 == m0;   // one tile per unit counts executed blocks
   if (a.route.sample_zeros) {
@@ -1241,7 +1248,7 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
       const bool nz = i < nloc && chunk_nonzero<C, PART>(a, nzvec, j);
       const uint64_t bal = __ballot(nz);
       const int before = __popcll(bal & ((1ull << lane) - 1ull));
-      if (nz) mine[total + before] = walk_entry<C, ESZ>(a, j);
+      if (nz) mine[total + before] = walk_entry<C, ESZ, PART>(a, j);
       total += __popcll(bal);
     }
     nloc = total;
@@ -1254,20 +1261,21 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
   const uint32_t ring =
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + wave * (S * STAGE);
   const char *const stages = smem + wave * (S * STAGE);
+  // PART: bit 31 where this lane's channels of a tap's last chunk lie past C_in
+  const int tail = PART ? (Cin - (a.cpt32 - 1) * C) * ESZ : ROW;
+  const uint32_t past = cg * 16 < tail ? 0u : 0x80000000u;
   auto load_chunk = [&](int i, int slot) __attribute__((always_inline)) {
-    const WalkStep e = walk_step(geom, mine[i]);
-    const int cb2 = PART ? e.kofs % (Cin * ESZ) : 0;
-    const bool col = !PART || cb2 + cg * 16 < Cin * ESZ;   // channels past C_in read zero
+    const WalkStep e = walk_step<PART>(geom, mine[i]);
     const uint32_t dst = ring + slot * STAGE;
 #pragma unroll
     for (int u = 0; u < 2 * TM; ++u) {
-      const uint32_t out = orow[u] << e.rsh | ocol[u] << e.ssh;
+      const uint32_t out = orow[u] << e.rsh | ocol[u] << e.ssh | (past & e.last);
       const uint32_t off = (uint32_t)(a_offb[u] + e.xofs) | (out & 0x80000000u);
-      load_to_lds(xr, dst + u * 1024, col ? (int)off : (int)0x80000000, 0);
+      load_to_lds(xr, dst + u * 1024, (int)off, 0);
     }
 #pragma unroll
     for (int u = 0; u < 2 * TN; ++u)
-      load_to_lds(wr, dst + BM * ROW + u * 1024, col ? b_offb[u] : (int)0x80000000, e.kofs);
+      load_to_lds(wr, dst + BM * ROW + u * 1024, b_offb[u] | (int)(past & e.last), e.kofs);
   };
   f32x4 acc[TM][TN];
 #pragma unroll
