@@ -858,6 +858,46 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
     count = list_len;
   }
 
+  // ---- the epilogue's bias and residual vectors: a lane holds channels 32 p +
+  // 8 g + [0, 8) of each block pair p, of pixel rl of its WTM pixel blocks.
+  // The 64 x 64 tile requests them behind the first chunks (its latency passes
+  // under the K loop), the others behind the K loop, before the first store (a
+  // load issued behind stores waits for them): 16 more registers through the K
+  // loop halve the resident waves of the 128 x 64 tile (30000 x 768 x 264 46 us
+  // and 74).
+  constexpr bool kEarly = WTM == 1 && NW == 4;
+  const int g = lane >> 4, rl = lane & 15;
+  const bool vec_n = N % 8 == 0;
+  const int mw = m0 + wm * WTM * 16 + rl, nw = n0 + wn * WTN * 16 + 8 * g;
+  const raw *bias = reinterpret_cast<const raw *>(a.bias);
+  const raw *res = reinterpret_cast<const raw *>(a.residual);
+  raw *y = reinterpret_cast<raw *>(a.y);
+  uint4 bias_q[NG][2], res_q[WTM][NG][2];
+  auto request_epilogue = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int col = nw + 64 * q + 32 * h;
+        bias_q[q][h] = uint4{0u, 0u, 0u, 0u};
+        if (bias && vec_n && col < N) bias_q[q][h] = *reinterpret_cast<const uint4 *>(bias + col);
+      }
+    if (res) {
+#pragma unroll
+      for (int tm = 0; tm < WTM; ++tm)
+#pragma unroll
+        for (int q = 0; q < NG; ++q)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int row = mw + 16 * tm, col = nw + 64 * q + 32 * h;
+            res_q[tm][q][h] = uint4{0u, 0u, 0u, 0u};
+            if (vec_n && row < M && col < N)
+              res_q[tm][q][h] =
+                  *reinterpret_cast<const uint4 *>(res + (int64_t)row * N + col);
+          }
+    }
+  };
+
   // ---- the K loop ----------------------------------------------------------
   const uint32_t ring =
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + wave * 1024;
@@ -886,7 +926,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
 #pragma unroll
     for (int j = 0; j < WTN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int g = lane >> 4, rl = lane & 15;
   const int fB = (((rl >> 2) & 1) << 2) | (rl & 3);
   int offA[2], offB[2];   // this lane's operand offsets of the two k-steps
 #pragma unroll
@@ -921,6 +960,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
   };
   const WalkGeom geom = walk_geom<2>(a);
   const int n = __builtin_amdgcn_readfirstlane(count);
+  if (kEarly && n == 0) request_epilogue();
   __syncthreads();   // the walk is written
   // One step per chunk.  On entry the step's operands are in registers (or
   // on their way from LDS).  After its barrier the next chunk's stage is
@@ -969,6 +1009,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
 #pragma unroll
         for (int u = 0; u < L; ++u) load_part(e, ring + s * STAGE, u);
       }
+    if (kEarly && a.split == 1) request_epilogue();
+    // (where they are requested the vectors are newer than the first chunks,
+    // so the first waits take more of the loads than they need)
     wait_chunks<S - 1, L>(min(S - 1, n - 1));
     asm volatile("s_barrier" ::: "memory");
     Operands p, q;
@@ -990,17 +1033,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
     }
   }
 
-  // ---- epilogue, from registers: a lane holds channels 32 p + 8 g + [0, 8)
-  // of each block pair p, of pixel rl of its WTM pixel blocks -- 16-byte
-  // vectors of bias, residual and output (four lanes of a pixel write 64
-  // consecutive bytes).  The residual vectors are requested before the first
-  // store (a load issued behind stores waits for them).
-  const bool vec_n = N % 8 == 0;
-  const int mw = m0 + wm * WTM * 16 + rl, nw = n0 + wn * WTN * 16 + 8 * g;
+  // ---- epilogue, from registers: 16-byte vectors of bias, residual and output
+  // (four lanes of a pixel write 64 consecutive bytes)
   uint32_t om_zeros = 0, om_nz = 0;
-  const raw *bias = reinterpret_cast<const raw *>(a.bias);
-  const raw *res = reinterpret_cast<const raw *>(a.residual);
-  raw *y = reinterpret_cast<raw *>(a.y);
   // Output rows that start anywhere (N % 8 != 0): a wave's blocks pass through
   // LDS in the ring's place, 16 pixels x 64 channels at a time, so that its
   // lanes store 64 consecutive channels element by element.  (Stored by the
@@ -1064,29 +1099,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void igemm_kernel(GemmArgs a) {
     }
     return;
   }
-  uint4 bias_q[NG][2], res_q[WTM][NG][2];
-#pragma unroll
-  for (int q = 0; q < NG; ++q)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int col = nw + 64 * q + 32 * h;
-      bias_q[q][h] = uint4{0u, 0u, 0u, 0u};
-      if (bias && col < N) bias_q[q][h] = *reinterpret_cast<const uint4 *>(bias + col);
-    }
-  if (res) {
-#pragma unroll
-    for (int tm = 0; tm < WTM; ++tm)
-#pragma unroll
-      for (int q = 0; q < NG; ++q)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int row = mw + 16 * tm, col = nw + 64 * q + 32 * h;
-          res_q[tm][q][h] = uint4{0u, 0u, 0u, 0u};
-          if (row < M && col < N)
-            res_q[tm][q][h] =
-                *reinterpret_cast<const uint4 *>(res + (int64_t)row * N + col);
-        }
-  }
+  if (!kEarly) request_epilogue();
   // output measurement (N % 64 == 0): the eight (1, 8) blocks of a pixel's
   // 64-channel group are one bitmap byte, met by two ballots
   const int mbytes = om && a.om_mask ? (int)(4 * (((int64_t)M * (N / 8) + 31) / 32)) : 0;
