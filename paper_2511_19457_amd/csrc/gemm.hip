@@ -594,9 +594,9 @@ __device__ __forceinline__ u32x4 buffer_words(const void *p, int64_t bytes) {
 
 // Tile walk of the second-generation kernels: work-group -> (K split, row
 // tile, column tile).  Work-groups are dealt round-robin to the 8 XCDs, so
-// XCD i gets the i-th contiguous range of tile ids, and a tile id walks
-// (split, column group, row tile, column tile of the group) with the column
-// tiles innermost: the tiles that gather the same input rows run together in
+// XCD i gets the i-th contiguous range of tile ids (SPREAD: every eighth),
+// and a tile id walks (split, column group, row tile, column tile of the
+// group) with the column tiles innermost: the tiles that gather the same input rows run together in
 // one XCD's L2.  The groups (host: ig_column_groups) keep an XCD to a part
 // of the weights where these are what its L2 would re-read.  (32-bit
 // arithmetic with float-reciprocal division: a 64-bit division by a runtime
@@ -605,11 +605,12 @@ __device__ __forceinline__ u32x4 buffer_words(const void *p, int64_t bytes) {
 struct TileId {
   int tile, zsplit, mt, nt;
 };
+template <bool SPREAD = false>
 __device__ __forceinline__ TileId tile_of(const GemmArgs &a) {
   TileId t;
   const int vid = (int)blockIdx.x, ntiles = (int)gridDim.x;
   // (XCD i holds the i-th range: q + 1 tiles for the first r XCDs, q after)
-  t.tile = (vid & 7) * (ntiles >> 3) + min(vid & 7, ntiles & 7) + (vid >> 3);
+  t.tile = SPREAD ? vid : (vid & 7) * (ntiles >> 3) + min(vid & 7, ntiles & 7) + (vid >> 3);
   int rest, grp;
   divmod_small(t.tile, a.ntmn32, a.inv_ntmn, t.zsplit, rest);
   divmod_small(rest, a.gt32, a.inv_gt, grp, rest);
@@ -1206,7 +1207,11 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
                "s"(a.route.counts), "s"(a.route.path_out), "s"(a.om_counts), "s"(a.nchunks));
   const bool om = a.om_counts != nullptr;
   const RouteCountsReq rq = route_counts_request(a.route);
-  const TileId tl = tile_of(a);
+  // (two waves, more tiles than CUs: an XCD's share is not one part of the
+  // rows, which with a padded batch would give one XCD all of the work; fp32
+  // 100352 x 64, 1024 channels, a quarter of the samples in use 164 us with a
+  // contiguous share, 54 so; all in use 170 either way)
+  const TileId tl = tile_of<NW == 2 && TM == 4>(a);
   const int m0 = a.row0 + tl.mt * BM, n0 = tl.nt * BN;
   const int M = (int)a.M, N = (int)a.N, n = (int)a.nchunks;
   const int H = (int)a.H, W = (int)a.W, Ho = (int)a.Ho, Wo = (int)a.Wo, Cin = (int)a.Cin;
@@ -2186,9 +2191,17 @@ LkTile lk_bitmap_tile(LkTile l, const Shape &s) {
 // waves have no work: 32 x 32 with two (2048 x 256 x 128 4.6 and 4.8).  Above
 // 512 chunks a wave's chain is longer than a split's (288 chunks 12.6 us and
 // 14.4, 0.24 and 0.19 us for each eight more).
-// fp32 has no other kernel with whole 128-byte chunks: 64 x 64 tiles beyond
-// these, four waves up to 256 tiles, else two (against the general kernel:
-// 1024^3 26.0 and 41.5 us; 2048^3 152 and 188; 6272 x 256 x 2304 86 and 121).
+// fp32 has no other kernel with whole 128-byte chunks, so 64 x 64 tiles beyond
+// these where they win: four waves up to 256 tiles, else two, two work-groups
+// a CU.  Against the general kernel, whose four work-groups a CU hide short
+// walks and ragged stores better (M x N x K, us): up to 256 tiles from 2
+// chunks (2488 x 256 x 32 8.6 and 7.7, x 64 8.8 and 8.9, x 512 16.6 and 23.3),
+// from 16 with ragged rows (3000 x 300 x 64 11.0 and 9.3, x 512 18.9 and 24.9);
+// up to 512 from 2 (6272 x 256 x 64 10.2 and 11.0, x 2048 77 and 109); up to
+// 1024 from 12, where their rounds of 512 tiles are as full as rounds of 256
+// (2048 x 2048 x 512 50 and 57, x 2048 149 and 187; 3000 x 1024 x 1152, 752
+// tiles, 89 and 87); beyond from 24 (42120 x 512 x 768 336 and 366, an input of
+// zeros only 72 and 52; x 512 243 and 254, zeros only 70 and 51).
 LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice &t, bool bitmap) {
   LkTile l;
   const bool f32 = d.dtype == SPAROA_F32;
@@ -2215,7 +2228,15 @@ LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice
   if (tiles(16, 64) <= 256) return take(kLk16x64, 16, 64);
   if (tiles(32, 64) <= 256)
     return chunks < 4 ? take(kLk32x32, 32, 32) : take(kLk32x64, 32, 64);
-  if (f32) return take(tiles(64, 64) <= 256 ? kLk64x64 : kLk64x64Many, 64, 64);
+  if (f32) {
+    const int64_t t64 = tiles(64, 64);
+    if (t64 <= 256)
+      return chunks >= (s.N % 8 == 0 ? 2 : 16) ? take(kLk64x64, 64, 64) : l;
+    const bool many = t64 <= 512    ? chunks >= 2
+                      : t64 <= 1024 ? chunks >= 12 && cdiv(t64, 256) % 2 == 0
+                                    : chunks >= 24;
+    if (many && s.N % 8 == 0) return take(kLk64x64Many, 64, 64);
+  }
   return l;
 }
 
