@@ -585,7 +585,7 @@ __device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t lds, int voffse
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
                : "s"(lds), "v"(voffset), "s"(rsrc), "s"(soffset)
-               : "memory");
+               : "memory", "m0");
 }
 __device__ __forceinline__ u32x4 buffer_words(const void *p, int64_t bytes) {
   const uint64_t b = reinterpret_cast<uint64_t>(p);
