@@ -579,13 +579,14 @@ __device__ __forceinline__ void wait_chunks(int chunks) {
 // compiler cannot tell the ring's stages apart and would wait for every load
 // in flight before each LDS read; the waits are written out at the barriers
 // instead (wait_loads).  No register is written, so the compiler's own
-// counting of other loads only waits longer than it has to.  (One wait state
-// between the write of m0 and its use.)
+// counting of other loads only waits longer than it has to.  (m0 is bound by
+// the operand, so the compiler knows what it holds; one wait state between its
+// write and its use.)
 __device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t lds, int voffset, int soffset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
-               : "s"(lds), "v"(voffset), "s"(rsrc), "s"(soffset)
-               : "memory", "m0");
+               : "{m0}"(lds), "v"(voffset), "s"(rsrc), "s"(soffset)
+               : "memory");
 }
 __device__ __forceinline__ u32x4 buffer_words(const void *p, int64_t bytes) {
   const uint64_t b = reinterpret_cast<uint64_t>(p);
