@@ -2029,11 +2029,16 @@ sparoa_status launch_small_c(const sparoa_conv_desc &d, const void *x, const voi
   // Output rows per work-group: weights are laid out once per work-group and
   // neighbouring rows share input rows, so 4 where that still leaves 384
   // work-groups, else 2, else 1 (ResNet-50's stem at N = 8, 896 rows: 2 rows
-  // 12.5 us, 1 row 17.9 us; at N = 1, 112 rows, latency).
+  // 12.5 us, 1 row 17.9 us; at N = 1, 112 rows, latency).  Where a row has
+  // fewer 16-pixel blocks than its share of the four waves, more rows cost a
+  // wave nothing: taken while there are more work-groups than CUs (7 x 7, 64
+  // channels, rows x Wo: 714 x 6 11.3 -> 6.5 us, 602 x 14 12.3 -> 7.0; at fewer
+  // work-groups a second block for a wave, 192 x 48 5.3 and 6.1).
   const int64_t rows = d.n * s.ho;
   const int wbytes = (4 * ksteps + 1) * (int)d.c_out * 16;
   auto patch_bytes = [&](int64_t rw) { return ((rw - 1) * d.sh + d.kh) * a.PWP * 8; };
   a.rw = rows >= 4 * 384 ? 4 : (rows >= 2 * 384 ? 2 : 1);
+  while (a.rw < 4 && cdiv(s.wo, 16) < 4 / a.rw && d.n * cdiv(s.ho, a.rw) > 256) a.rw *= 2;
   while (a.rw > 1 && wbytes + patch_bytes(a.rw) > kScLdsBytes) a.rw /= 2;
   a.prows = (a.rw - 1) * a.sh + a.kh;
   const int64_t both = wbytes + patch_bytes(a.rw);
