@@ -2209,7 +2209,16 @@ LkTile lk_bitmap_tile(LkTile l, const Shape &s) {
 // (2048 x 2048 x 512 50 and 57, x 2048 149 and 187; 3000 x 1024 x 1152, 752
 // tiles, 89 and 87); beyond from 24 (42120 x 512 x 768 336 and 366, an input of
 // zeros only 72 and 52; x 512 243 and 254, zeros only 70 and 51).
-LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice &t, bool bitmap) {
+// Measured without commit words (`direct`), each work-group's two atomics on
+// the counters take their turn, 28 ns: above 80 work-groups, 128 from 3 chunks
+// and 192 from 9, a layer whose K the 64-row tiles do not split runs in those,
+// about a quarter as many (M x N x K, us: 3136 x 128 x 128 14.7 in 392 of the
+// few-tile kernel, 7.9 in 98; 784 x 512 x 128 16.0 in 400, 9.2 in 104; 3136 x 64
+// x 512 10.1 in 196, 8.6 in 49; 49 x 256 x 512 5.8 in 64, 7.7 in 4; 196 x 128 x
+// 1152 7.1 in 104, 9.2 in 8).  Where they split K, and a reduction follows, the
+// few-tile kernel stays ahead (196 x 512 x 4608 11.8 in 208, 15.2).
+LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice &t, bool bitmap,
+                 bool direct) {
   LkTile l;
   const bool f32 = d.dtype == SPAROA_F32;
   const int64_t c = f32 ? kBK : kBK2, chunks = d.kh * d.kw * cdiv(d.c_in, c);
@@ -2223,6 +2232,9 @@ LkTile lk_choose(const sparoa_conv_desc &d, const Shape &s, const GemmTileChoice
     return l;
   }
   auto take = [&](int cfg, int bm, int bn) {
+    if (direct && t.split_k == 1 &&
+        cdiv(s.M, bm) * cdiv(s.N, bn) > (chunks < 3 ? 80 : chunks < 9 ? 128 : 192))
+      return LkTile{};
     l.cfg = cfg;
     l.bm = bm;
     l.bn = bn;
@@ -2406,7 +2418,8 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
   // the few-tile kernel splits K inside a work-group; the workspace that the
   // query names is asked for all the same
   const bool bitmap = om && om->mask;
-  const LkTile lk = lk_choose(d, s, t, bitmap);
+  const bool direct = om && !om->words;
+  const LkTile lk = lk_choose(d, s, t, bitmap, direct);
   const int64_t splits = cdiv(nchunks, a.chunks_per_split), gz = lk.cfg ? 1 : splits;
   a.split = (int)gz;
   // the epilogue measures y when it writes y; with split-K the reduction does
@@ -2476,7 +2489,7 @@ sparoa_status launch_gemm_conv(const sparoa_conv_desc &d, sparoa_path path, cons
       Shape rest = s;
       rest.M = s.M - head;
       const GemmTileChoice u = ig_choose(rest, d.c_in);
-      ok = launch_rows(head, rest.M, lk_choose(d, rest, u, bitmap), u);
+      ok = launch_rows(head, rest.M, lk_choose(d, rest, u, bitmap, direct), u);
     }
   } else {
     const dim3 grid((unsigned)cdiv(s.M, t.bm), (unsigned)cdiv(s.N, t.bn), (unsigned)gz);
