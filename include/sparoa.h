@@ -377,18 +377,19 @@ sparoa_status sparoa_fc_routed(const sparoa_fc_desc *desc, const sparoa_threshol
  *   -- the block shape every conv and MFMA-family FC consumer skips at.
  *   y_mask holds sparoa_mask_words(rows, cols, 1, 8) words and needs no
  *   clearing.  y_mask NULL: counts only -- all four counts, no bitmap (for a
- *   consumer that routes on the counts and reads no bitmap); cols % 8 == 0.  The depthwise kernel's counts-only form is its plain
- *   kernel with per-lane counting; with y_mask it runs one output vector
- *   per lane so that a wave's bits are two whole bitmap words.
+ *   consumer that routes on the counts and reads no bitmap); cols % 8 == 0.
+ *   The depthwise kernel's counts-only form is its plain kernel with per-lane
+ *   counting; with y_mask it runs one output vector per lane so that a wave's
+ *   bits are two whole bitmap words.
  *   y_counts must hold {0, rows*cols, nb, nb} on entry, nb = rows*ceil(cols/8):
  *   the fused form adds into it (a caller resets all of a network's counters
  *   with one copy from a template before each pass).
  *   Fused into the producer's epilogue (or its split-K reduction) where the
  *   kernel that serves the layer can (the 64-channel-chunk implicit GEMM --
  *   16-bit, C_in % 64 == 0 or C_in % 8 == 0 with C_in >= 48 -- with
- *   cols % 64 == 0, or cols % 8 == 0 where it splits K and its reduction
- *   writes y; the pointwise kernel with one weight slice; the depthwise
- *   and image-stem kernels, counts only for the stem): no launch of
+ *   cols % 64 == 0, or cols % 8 == 0 where the workspace query names partial
+ *   sums for the layer; the pointwise kernel with one weight slice; the
+ *   depthwise and image-stem kernels, counts only for the stem): no launch of
  *   its own and no second read of y; otherwise the standalone measurement of
  *   y runs after the layer (as sparoa_measure_sparsity_preset with y_commit:
  *   one launch for the block shapes whose bitmap needs no clearing).
@@ -400,7 +401,9 @@ sparoa_status sparoa_fc_routed(const sparoa_fc_desc *desc, const sparoa_threshol
  *   word per count from 2^27 elements up; the work-group completing a group
  *   adds the group's total to y_counts and clears the word) instead of one
  *   same-address atomic per work-group on y_counts.  NULL: direct commits,
- *   same counts.  Calls that overlap in time must not share y_commit.
+ *   the counts of the y written (whose last bits may differ from those of a
+ *   call with words: K may be summed in another order).  Calls that overlap
+ *   in time must not share y_commit.
  *   Other arguments as for sparoa_conv2d_routed / sparoa_fc_routed.
  * Errors: theirs, and INVALID_ARG for a null y_counts, or a NULL y_mask
  * where cols % 8 != 0.

@@ -537,7 +537,7 @@ __global__ __launch_bounds__(256) void split_reduce_group(ReduceGroup g) {
 // that refill the stage freed by the barrier, between the MFMAs of the chunk
 // before.  The MFMA's rows are channels, so a lane ends with 8 consecutive
 // output channels of a pixel per block pair, four lanes with 32, and the
-// epilogue needs no LDS.
+// epilogue needs no LDS (but for output rows that start anywhere, C_out % 8).
 // Bounds, measured with the other parts switched off (4096^3 fp16, 128 x 256:
 // 117 us): MFMAs alone 97 us (1.6 PFLOP/s with its start and end), loads
 // alone 95 us (17 TB/s out of the L2s); small tiles are bound by the loads
@@ -578,7 +578,7 @@ __device__ __forceinline__ void wait_chunks(int chunks) {
 // past the descriptor's range.  In assembly and not by the builtin: the
 // compiler cannot tell the ring's stages apart and would wait for every load
 // in flight before each LDS read; the waits are written out at the barriers
-// instead (wait_loads).  No register is written, so the compiler's own
+// instead (wait_chunks).  No register is written, so the compiler's own
 // counting of other loads only waits longer than it has to.  (m0 is bound by
 // the operand, so the compiler knows what it holds; one wait state between its
 // write and its use.)
@@ -1382,8 +1382,7 @@ __global__ __launch_bounds__(64 * NW, 2) void igemm_lk_kernel(GemmArgs a) {
 
   // ---- the partial tiles meet in LDS, in the rings' place (a lane holds 4
   // consecutive channels 4 g + [0, 4) of pixel rl of each block)
-  if (NW > 1) __syncthreads();
-  else asm volatile("" ::: "memory");
+  __syncthreads();
   float *const red = reinterpret_cast<float *>(smem);
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm)
@@ -2307,7 +2306,7 @@ GemmTileChoice gemm_choose(const sparoa_conv_desc &d, sparoa_path path) {
     return t;
   }
   if (ig_eligible(d)) return ig_choose(s, d.c_in);
-  if (small_c_eligible(d)) {   // one output row per work-group, 16-pixel row blocks
+  if (small_c_eligible(d)) {   // up to four output rows per work-group, 16-pixel row blocks
     t.cfg = 0;
     t.bm = 16;
     t.bn = 16;
@@ -2346,12 +2345,16 @@ bool gemm_fuses_out_measure(const sparoa_conv_desc &d, sparoa_path path, bool bi
   if (t.pointwise) return pw_fuses_out_measure(d);
   // the small-channel kernel counts (no bitmap)
   if (t.small_c) return !bitmap;
-  // the second-generation kernel (64-column tiles) writes whole bitmap bytes
-  // when C_out % 64 == 0; its split-K reduction measures 16-byte vectors (a
-  // wave's 64 vectors are two whole bitmap words), any C_out % 8 == 0
+  // every tile writes whole bitmap bytes, or sets its bits, when C_out % 64 ==
+  // 0.  Else the layers whose K the 64-row tiles split, at any C_out % 8 == 0:
+  // the reduction measures 16-byte vectors (a wave's 64 vectors are two whole
+  // bitmap words), and the few-tile kernel, which takes most of these layers
+  // without a split, its 8-channel blocks.  (It could measure its unsplit
+  // layers as well; the 64-column tiles, which take them when they are measured
+  // without commit words, could not.)
   if (t.cfg == 0 || elem_size(d.dtype) != 2) return false;
   if (d.c_out % 64 == 0) return true;
-  // the K splits the launch will take (as launch_gemm_conv counts them)
+  // the K splits of the 64-row tiles (as launch_gemm_conv counts them)
   const int64_t nchunks = d.kh * d.kw * cdiv(d.c_in, t.kchunk);
   const int64_t gz = cdiv(nchunks, cdiv(nchunks, t.split_k));
   return gz > 1 && d.c_out % 8 == 0;

@@ -594,7 +594,7 @@ void launch_main(dim3 grid, hipStream_t st, const void *x, int64_t cols, int64_t
 // Without them each work-group's two same-address atomics take their turn, 28
 // ns, behind the pass: about sqrt(items) / 7 work-groups balance the two
 // (6.4 MB: 96 7.8 us, 256 10.4, 32 10.3; 25.7 MB: 192 12.2, 256 13.0, 96 13.8).
-int64_t lanebit_grid(int64_t items, bool commit) {
+static int64_t lanebit_grid(int64_t items, bool commit) {
   int64_t gx = cdiv(items, (int64_t)kLanebitThreads);
   if (gx > 512) gx = 512;
   if (!commit) {

@@ -34,8 +34,9 @@
 //
 // Output measurement (Section 3.1, Eq. 1, taken on the layer's output): with
 // one slice the epilogue also counts the zeros of y and builds its bitmap at
-// block (1 pixel, 8 channels); a tile's bitmap words meet in LDS (tiles start
-// on 32-bit word boundaries) and leave as whole-word stores.
+// block (1 pixel, 8 channels).  Where a pixel's blocks are whole bytes its bytes
+// come from ballots; else a tile's bitmap words meet in LDS (tiles start on
+// 32-bit word boundaries) and leave as whole-word stores.
 #include "commit.h"
 #include "common.h"
 #include "dtype.h"
@@ -85,7 +86,11 @@ __device__ __forceinline__ void divmod_f(int n, int d, float inv_d, int &q, int 
 // Waves per SIMD asked of the compiler: three where the accumulators and the
 // two tiles of activations leave room (144 -> 24 at 56 x 56, N = 32 13.2 ->
 // 11.9 us), else two (64 -> 256 with residual: two 34 us, three 37 us, four
-// spill; without a bound it took 284 registers, one wave, 51 us).
+// spill; without a bound it took 284 registers, one wave, 51 us).  The residual
+// vectors are left out of the count: with 16 blocks and one k-step they make
+// three waves spill 10 registers (44 bytes a lane), which costs less than the
+// third wave gains (16 -> 256 with residual at 56 x 56, N = 37 27.3 us, 29.7
+// with two; 30 such shapes 1.02x).
 constexpr int pw_waves(int nb, int r, int ks) { return r * nb * 4 + 8 * r * ks <= 72 ? 3 : 2; }
 
 template <int DT, int NB, int R, int KS, bool RES>
@@ -446,8 +451,6 @@ const void *pw_kernel(int nb, int r, int ks, bool res) {
   return nullptr;
 }
 
-// Work-groups of `fn` that fit on the current device at once (occupancy
-// query, cached per device, kernel and LDS size).
 }  // namespace
 
 bool pw_eligible(const sparoa_conv_desc &d) {
