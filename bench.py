@@ -23,7 +23,8 @@ step).
 value = dense-equivalent TFLOP/s of the step: sum over operators of
 2 m k n divided by the step time (skipped work counts as done).
 
-Prints one JSON line on stdout.
+Prints one JSON line on stdout (its long tables, per case and per layer, on
+stderr).
 """
 import argparse
 import hashlib
@@ -1600,6 +1601,16 @@ def main():
     if args.cases_out:
         with open(args.cases_out, "w") as f:
             json.dump(table, f, indent=1)
+    emit(line)
+
+
+def emit(line):
+    """The result as one JSON line on stdout.  Its long tables (every case of
+    the sweep, every layer of the models; nine tenths of the text) go to stderr
+    as a JSON line of their own, so that the result is whole in a record that
+    keeps the last few KB of the output."""
+    tables = {k: line.pop(k) for k in ("sweep", "layers") if k in line}
+    print("bench: tables " + json.dumps(tables), file=sys.stderr, flush=True)
     print(json.dumps(line), flush=True)
 
 

@@ -66,3 +66,12 @@ def test_committed_thresholds_file():
     assert sorted(thr) == list(bench.M_LIST)
     for s_thr, c_thr in thr.values():
         assert 0.0 < s_thr <= 1.0 and c_thr > 0.0
+
+
+def test_result_line_without_tables(capsys):
+    bench.emit(dict(metric="m", value=1.0, sweep=[dict(us=1.0)] * 24,
+                    layers=dict(stack=dict(rows=[dict(us=2.0)] * 54))))
+    out, err = capsys.readouterr()
+    assert json.loads(out) == dict(metric="m", value=1.0) and out.count("\n") == 1
+    tables = json.loads(err.split("bench: tables ")[1])
+    assert len(tables["sweep"]) == 24 and len(tables["layers"]["stack"]["rows"]) == 54
