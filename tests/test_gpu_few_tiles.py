@@ -31,7 +31,7 @@ SHAPES = [
     # 32 x 32 (under 4 chunks) and 32 x 64, stride and dilation
     (1, 128, 1, 2047, 256, 1, 1, 0, 1), (5, 128, 45, 39, 128, 3, 2, 1, 1),
     (2, 64, 60, 61, 64, 3, 1, 2, 2),
-    # beyond them: 64 x 64 in fp32 (four waves, two)
+    # beyond them: 64 x 64 in fp32 (four waves), 528 tiles (the general kernel)
     (1, 320, 1, 4100, 192, 1, 1, 0, 1), (3, 64, 75, 75, 72, 3, 1, 1, 1),
     # partial chunks at 16 bits (C_in % 64 != 0)
     (1, 72, 14, 14, 40, 3, 1, 1, 1), (1, 48, 1, 300, 128, 1, 1, 0, 1),

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 # n, cin, h, w, cout, kh, kw, sh, sw, ph, pw
 SHAPES = [
-    (7, 3, 218, 64, 64, 7, 7, 2, 2, 3, 3),      # 763 rows: 1 per work-group
+    (7, 3, 218, 64, 64, 7, 7, 2, 2, 3, 3),      # 763 rows: 2 per work-group, two blocks a row
     (7, 3, 219, 64, 64, 7, 7, 2, 2, 3, 3),      # 770 rows: 2, ragged
     (14, 3, 219, 50, 64, 7, 7, 2, 2, 3, 3),     # 1540 rows: 4, ragged, odd Wo
     (14, 3, 221, 51, 32, 3, 3, 2, 2, 1, 1),     # W C odd: element loads
